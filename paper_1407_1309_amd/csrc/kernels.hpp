@@ -9,6 +9,15 @@
 
 namespace mp {
 
+// What the chip holds of a kernel at once: compute units and workgroups per
+// unit (from the runtime's occupancy query; the figures of a gfx950, 256
+// units and one workgroup, if it fails).  For the rules that choose how much
+// of a grid one workgroup takes; results never depend on it.
+struct Slots {
+    int cus, per_cu;
+};
+Slots slots_of(const void *kernel, int threads, size_t lds = 0);
+
 // Arguments of one step through the staged (one launch per stage) path.
 template <typename T> struct StagedArgs {
     Geom g;

@@ -448,6 +448,21 @@ int64_t wall_count(const Geom &g, int d)
 
 }  // namespace
 
+Slots slots_of(const void *kernel, int threads, size_t lds)
+{
+    Slots v{256, 1};
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds) == hipSuccess) {
+        if (cus > 0) v.cus = cus;
+        if (per > 0) v.per_cu = per;
+    } else {
+        (void)hipGetLastError();
+    }
+    return v;
+}
+
 // ---- single-stage launchers (used by the adjoint's forward recompute) ----
 template <typename T>
 hipError_t launch_donor(const Geom &g, const T *x, const T *const c[3], const T *G,

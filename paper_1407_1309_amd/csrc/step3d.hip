@@ -124,8 +124,14 @@ __device__ __forceinline__ int64_t box_offset(int e, int n_e, int w, int jb, int
     return j * row_len + k;
 }
 
+// In FP32 a workgroup's rings take at most 74 KB of LDS, so two fit a CU if
+// its registers let them: the bound of four waves per SIMD (128 VGPRs) costs
+// the third-order instances a few spilled registers (124-172 without it) and
+// lets the second workgroup cover the first one's barriers: FP32 tot + iga +
+// G, 256^3, 64-plane chunks, 366 -> 246 us per step; the instances without
+// third-order terms fitted already.  In FP64 the rings allow one workgroup.
 template <typename T, bool HAS_G, bool IGA, bool ABS, bool DFL, bool TOT, bool XIN, bool BETA>
-__global__ void __launch_bounds__(NT) k_step3d(G3s g, int th, int tiles_k, int tiles_j, int nblk,
+__global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) k_step3d(G3s g, int th, int tiles_k, int tiles_j, int nblk,
                                                int kahan, const T *__restrict__ x,
                                                const T *__restrict__ c0,
                                                const T *__restrict__ c1,
@@ -729,6 +735,40 @@ __global__ void __launch_bounds__(NT) k_step3d(G3s g, int th, int tiles_k, int t
     }
 }
 
+// Planes per chunk when the caller set none.  A workgroup's time is its
+// planes plus the warm-up and start-up of its march (about PL_EXTRA planes'
+// worth), and the launch takes as many rounds as the workgroups need on the
+// chip's slots; a CU's second workgroup (FP32) costs about half of a first
+// one.  For each number of rounds the most chunks that fit it are priced and
+// the cheapest is taken.  Every size swept (4 to 128 planes) came out within
+// 5 % of its best chunk.  us per step, a fixed 96 planes -> the rule: FP64,
+// tot + iga + G: 384 x 384 x 256 1068 -> 1068 (96 planes, three rounds),
+// 256^3 704 -> 468, 101 x 130 x 67 333 -> 60, 32^3 120 -> 31; FP32 with the
+// limiter: 101 x 130 x 67 291 -> 60, 200 x 200 x 100 324 -> 162.
+constexpr int PL_EXTRA = 5, PL_MIN = 4, MAX_ROUNDS = 12;
+
+int planes_per_chunk(int64_t tiles, int n0, int cus, int per_cu)
+{
+    const int64_t slots = (int64_t)cus * per_cu;
+    int best = n0;
+    double best_cost = 0.0;
+    for (int rounds = 1; rounds <= MAX_ROUNDS; rounds++) {
+        int64_t chunks = rounds * slots / tiles;
+        if (chunks > cdiv(n0, PL_MIN)) chunks = cdiv(n0, PL_MIN);
+        if (chunks < 1) chunks = 1;
+        const int th = (int)cdiv(n0, chunks);
+        const int64_t wgs = tiles * cdiv(n0, th), rest = wgs % slots;
+        auto load = [&](int64_t per) { return 0.5 * (double)(per + 1); };   // a CU with `per` workgroups
+        const double cost = (th + PL_EXTRA) * ((double)(wgs / slots) * load(per_cu) +
+                                               (rest ? load(cdiv(rest, cus)) : 0.0));
+        if (rounds == 1 || cost < best_cost) {
+            best_cost = cost;
+            best = th;
+        }
+    }
+    return best;
+}
+
 }  // namespace
 
 bool step3d_supported(int nd, int n_iters, unsigned opts, const int64_t n[3])
@@ -750,19 +790,28 @@ hipError_t step3d_launch(const Geom &geom, unsigned opts, const T *psi_n, T *psi
     if (vo.bup && (!vo.bdn || !vo.v0)) return hipErrorInvalidValue;
     G3s g{(int)geom.n[0], (int)geom.n[1], (int)geom.n[2], geom.bc[0], geom.bc[1], geom.bc[2]};
     const int tiles_k = (g.n2 + SK - 1) / SK, tiles_j = (g.n1 + SJ - 1) / SJ;
-    int th = tile_planes > 0 ? tile_planes : 96;
-    if (th > g.n0) th = g.n0;
-    const int64_t chunks = cdiv(g.n0, th);
-    const int64_t blocks = (int64_t)tiles_k * tiles_j * chunks;
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const int64_t tiles = (int64_t)tiles_k * tiles_j;
+    hipError_t err = hipSuccess;
     const int kahan = (opts & OPT_KAHAN) ? 1 : 0;
     const bool iga = opts & OPT_IGA, absf = opts & OPT_ABS, dfl = opts & OPT_DFL,
                tot = opts & OPT_TOT;
     auto go = [&](auto HG, auto IG, auto AB, auto DF, auto TO, auto XI, auto BE) {
-        k_step3d<T, decltype(HG)::value, decltype(IG)::value, decltype(AB)::value,
-                 decltype(DF)::value, decltype(TO)::value, decltype(XI)::value,
-                 decltype(BE)::value><<<(unsigned)blocks, NT, 0, s>>>(
-            g, th, tiles_k, tiles_j, (int)blocks, kahan, psi_n, c0, c1, c2, G, psi_out, vo);
+        auto kern = k_step3d<T, decltype(HG)::value, decltype(IG)::value, decltype(AB)::value,
+                             decltype(DF)::value, decltype(TO)::value, decltype(XI)::value,
+                             decltype(BE)::value>;
+        int th = tile_planes;
+        if (th <= 0) {
+            static const Slots slots = slots_of((const void *)kern, NT);
+            th = planes_per_chunk(tiles, g.n0, slots.cus, slots.per_cu);
+        }
+        if (th > g.n0) th = g.n0;
+        const int64_t blocks = tiles * cdiv(g.n0, th);
+        if (blocks > INT32_MAX) {
+            err = hipErrorInvalidValue;
+            return;
+        }
+        kern<<<(unsigned)blocks, NT, 0, s>>>(g, th, tiles_k, tiles_j, (int)blocks, kahan, psi_n,
+                                             c0, c1, c2, G, psi_out, vo);
     };
     using TT = std::true_type;
     using FF = std::false_type;
@@ -791,7 +840,7 @@ hipError_t step3d_launch(const Geom &geom, unsigned opts, const T *psi_n, T *psi
     };
     if (G) by_m(TT{});
     else by_m(FF{});
-    return hipGetLastError();
+    return err != hipSuccess ? err : hipGetLastError();
 }
 
 template hipError_t step3d_launch<float>(const Geom &, unsigned, const float *, float *,
