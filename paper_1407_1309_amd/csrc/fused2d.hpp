@@ -23,6 +23,8 @@
 #include "common.hpp"
 #include "kernels.hpp"
 
+#include <type_traits>
+
 // Multiply-add contraction only within one source expression (decided by the
 // front end from the source alone).  The kernel body is instantiated twice
 // (fast and safe quotient modes, see qset); with contraction left to the
@@ -607,36 +609,32 @@ __global__ void __launch_bounds__(WAVE) k_fused2d_batched(const BatchGrid *__res
                                            nullptr, 0);
 }
 
-// default rows per chunk (when not tuned): about two waves per SIMD, so the
-// chip is full while the warm-up rows stay a modest fraction
-int64_t rows_per_chunk(int64_t n0, int64_t strips)
-{
-    int64_t target_waves = 2048;
-    int64_t chunks = target_waves / (strips > 0 ? strips : 1);
-    if (chunks < 1) chunks = 1;
-    int64_t th = cdiv(n0, chunks);
-    if (th < 16) th = 16;
-    return th;
-}
-
 template <typename T, int NI, bool FCT, bool ABS, bool KH>
 hipError_t launch(const Fused2DShape &sh, const T *psi_n, T *psi_out, const T *c0,
                   const T *c1, double *dpart, int *dparts, hipStream_t s)
 {
     using C = Cfg<NI, FCT>;
     int64_t strips = cdiv(sh.n1, C::OW);
-    int64_t th = sh.tile_rows > 0 ? sh.tile_rows : rows_per_chunk(sh.n0, strips);
-    if (th > sh.n0) th = sh.n0;
-    int64_t chunks = cdiv(sh.n0, th);
-    int64_t blocks = strips * chunks;
-    if (dpart) {
+    auto go = [&](auto DG) {
+        auto kern = k_fused2d<T, NI, FCT, ABS, KH, decltype(DG)::value>;
+        int64_t th = sh.tile_rows;
+        if (th <= 0) {
+            // a chunk runs th + 2 LAG + 1 iterations, the warm-up ones
+            // (W) at part of the work; one with diagnostics is at least as
+            // long as the partials' buffer allows for
+            static const Slots slots = slots_of((const void *)kern, WAVE);
+            constexpr int W = C::NP == 0 ? 0 : 4 * C::NP - 1;
+            th = march_rows(sh.n0, strips, slots, 2 * C::LAG + 1 - W, C::UT,
+                            decltype(DG)::value ? 16 : 4, 0.75 * W);
+        }
+        if (th > sh.n0) th = sh.n0;
+        const int64_t blocks = strips * cdiv(sh.n0, th);
         if (dparts) *dparts = (int)blocks;
-        k_fused2d<T, NI, FCT, ABS, KH, true><<<(unsigned)blocks, WAVE, 0, s>>>(
-            (int)sh.n0, (int)sh.n1, (int)th, (int)strips, psi_n, psi_out, c0, c1, dpart);
-    } else {
-        k_fused2d<T, NI, FCT, ABS, KH, false><<<(unsigned)blocks, WAVE, 0, s>>>(
-            (int)sh.n0, (int)sh.n1, (int)th, (int)strips, psi_n, psi_out, c0, c1, nullptr);
-    }
+        kern<<<(unsigned)blocks, WAVE, 0, s>>>((int)sh.n0, (int)sh.n1, (int)th, (int)strips, psi_n,
+                                               psi_out, c0, c1, dpart);
+    };
+    if (dpart) go(std::true_type{});
+    else go(std::false_type{});
     return hipGetLastError();
 }
 

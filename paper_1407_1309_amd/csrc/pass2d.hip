@@ -195,7 +195,7 @@ template <bool TOT> constexpr int unroll() { return TOT ? 8 : 4; }
 // dimension-0 walls); otherwise x is loaded.  With open boundaries the donor
 // result of a cell outside the domain is the edge cell's: edge lanes are
 // copied across (readlane), rows past the end repeat the last row, and the
-// first chunk starts at row 0 with the rows above filled with row 0.
+// first chunks start at row 0 with the rows above filled with row 0.
 // HG: G is an array (loaded with the cell rows, row a at age CO); otherwise
 // G = 1.
 template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT> struct March {
@@ -669,9 +669,10 @@ __global__ void __launch_bounds__(WAVE)
     // i0-2: loaded as the newest wall at iteration i0-3.  Without the donor
     // pass, cell rows are loaded from a and dimension-0 walls one row
     // ahead; with it, psi^n, c1 and the walls all one row ahead, and the
-    // rings start with rows a-1 and a.  The first chunk of an open domain
-    // starts at row 0 (the rows above are copies of row 0).
-    m.prefill = DONOR && bc0 == BC_OPEN && i0 == 0;
+    // rings start with rows a-1 and a.  A chunk of an open domain whose first
+    // iteration would lie above row 0 starts at row 0 (the rows above are
+    // copies of row 0).
+    m.prefill = DONOR && bc0 == BC_OPEN && i0 < 3;
     const int a_begin = m.prefill ? 0 : i0 - 3;
     const int a_end = i1 + 1 + M::SH;
     if (DONOR) {
@@ -727,22 +728,6 @@ __global__ void __launch_bounds__(DB)
     if (copy) copy[r + j] = xc;
 }
 
-// Default rows per chunk: about four waves per SIMD (the FP64 kernels hold
-// 4-5 waves per SIMD), at least 11 rows, and a chunk length whose iteration
-// count (rows + 5 + sh) is a whole number of unrolled blocks of u rows.
-int64_t chunk_rows(int64_t n0, int64_t strips, int tile_rows, int u, int sh)
-{
-    int64_t th = tile_rows;
-    if (th <= 0) {
-        int64_t chunks = 4096 / (strips > 0 ? strips : 1);
-        if (chunks < 1) chunks = 1;
-        th = cdiv(n0, chunks);
-        if (th < 11) th = 11;
-        th = cdiv(th + 5 + sh, u) * u - 5 - sh;
-    }
-    return th > n0 ? n0 : th;
-}
-
 template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT>
 hipError_t launch(const Geom &g, unsigned opts, const T *x, const T *c0, const T *c1,
                   const T *psi_n, const T *G, T *y, T *w0, T *w1, const PassRecord<T> &rec,
@@ -750,9 +735,16 @@ hipError_t launch(const Geom &g, unsigned opts, const T *x, const T *c0, const T
 {
     const int64_t n0 = g.n[0], n1 = g.n[1];
     const int64_t strips = cdiv(n1, Lanes<DONOR, TOT>::OW);
-    const int64_t th = chunk_rows(n0, strips, tile_rows, unroll<TOT>(), TOT ? 1 : 0);
+    auto kern = k_pass2d<T, FCT, IGA, ABS, DONOR, HG, TOT>;
+    int64_t th = tile_rows;
+    if (th <= 0) {
+        // a chunk runs th + 5 iterations (one more under TOT)
+        static const Slots slots = slots_of((const void *)kern, WAVE);
+        th = march_rows(n0, strips, slots, TOT ? 6 : 5, unroll<TOT>(), 1);
+    }
+    if (th > n0) th = n0;
     const int64_t blocks = strips * cdiv(n0, th);
-    k_pass2d<T, FCT, IGA, ABS, DONOR, HG, TOT><<<(unsigned)blocks, WAVE, 0, s>>>(
+    kern<<<(unsigned)blocks, WAVE, 0, s>>>(
         (int)n0, (int)n1, g.bc[0], g.bc[1], (int)th, (int)strips, (opts & OPT_DFL) ? 1 : 0,
         (opts & OPT_KAHAN) ? 1 : 0, x, c0, c1, psi_n, G, y, w0, w1, rec.v0, rec.v1, rec.bu,
         rec.bd, rec.xd);
