@@ -228,9 +228,15 @@ void timer_end(mpdata_plan *p)
     if (p->t_launches == p->t_limit) (void)hipEventRecord(p->tev[1], p->stream);
 }
 
-// kernels of one step: stage by stage, the whole-step fused kernels, or the
-// donor pass plus one launch per corrective pass (2-D)
-enum { PATH_STAGED = 0, PATH_FUSED = 1, PATH_PASS2D = 2 };
+// kernels of one step: stage by stage, the whole-step fused kernels, the
+// donor pass plus one launch per corrective pass (2-D), or the 1-D tiles
+enum { PATH_STAGED = 0, PATH_FUSED = 1, PATH_PASS2D = 2, PATH_LINE = 3 };
+
+template <typename T> mp::LineArgs<T> line_args(const mpdata_plan *p, const T *c, const T *G,
+                                                double osc_a = 0.0)
+{
+    return mp::LineArgs<T>{p->g.n[0], p->g.bc[0], p->desc.n_iters, p->desc.opts, c, G, osc_a};
+}
 
 template <typename T>
 int one_step(mpdata_plan *p, const T *psi_n, T *psi_out, const T *G, const T *c0, const T *c1,
@@ -239,6 +245,7 @@ int one_step(mpdata_plan *p, const T *psi_n, T *psi_out, const T *G, const T *c0
     hipError_t e = hipSuccess;
     const bool fused = path == PATH_FUSED;
     const char *name = path == PATH_PASS2D ? "k_pass2d"
+                       : path == PATH_LINE ? "k_resident1d"
                        : !fused            ? "staged step"
                        : p->desc.n_dims == 3
                            ? (p->desc.n_iters == 1 ? "k_donor3d" : "k_step3d")
@@ -263,6 +270,12 @@ int one_step(mpdata_plan *p, const T *psi_n, T *psi_out, const T *G, const T *c0
             set ^= 1;
             x = y;
         }
+    } else if (path == PATH_LINE) {
+        int launches = 0;
+        const mp::LineShape sh = mp::line1d_tiled(p->g.n[0], sizeof(T) == 8, p->desc.n_iters,
+                                                  p->desc.opts, 1, 1, &launches);
+        e = mp::line1d_launch<T>(sh, line_args<T>(p, c0, G), 1, psi_n, nullptr, psi_out, nullptr,
+                                 p->stream);
     } else if (fused && p->desc.n_dims == 3) {
         mp::Fused3DWork<T> w;
         for (int k = 0; k < 2; k++) {
@@ -327,14 +340,67 @@ bool use_pass2d(const mpdata_plan *p)
                                 p->g.n);
 }
 
+// (the 1-D grids that fit one workgroup are use_resident's)
 int step_path(const mpdata_plan *p)
 {
-    return use_fused(p) ? PATH_FUSED : use_pass2d(p) ? PATH_PASS2D : PATH_STAGED;
+    return use_fused(p)    ? PATH_FUSED
+           : use_pass2d(p) ? PATH_PASS2D
+           : p->desc.n_dims == 1 && p->kernel != MPDATA_KERNEL_STAGED ? PATH_LINE
+                                                                      : PATH_STAGED;
 }
 
 bool use_resident(const mpdata_plan *p)
 {
     return p->kernel != MPDATA_KERNEL_STAGED && resident_available(p);
+}
+
+// all steps of a call on a 1-D grid that one workgroup holds, in place
+template <typename T>
+hipError_t resident_steps(mpdata_plan *p, T *psi, T *phi, const T *c, const T *G, int n_steps,
+                          double osc_a = 0.0)
+{
+    return mp::line1d_launch<T>(mp::line1d_whole(p->g.n[0], p->desc.n_iters, p->desc.opts),
+                                line_args<T>(p, c, G, osc_a), n_steps, psi, phi, psi, phi,
+                                p->stream);
+}
+
+// n_steps steps (> 0) of psi, and of phi for the oscillator pair, on a longer
+// 1-D grid: tiled launches of several steps each, between the caller's
+// buffers and the workspace's (an even number of launches, or one from a
+// copy)
+template <typename T>
+int line_steps(mpdata_plan *p, T *psi, T *phi, const T *c, const T *G, int n_steps,
+               double osc_a = 0.0)
+{
+    int launches = 0;
+    const mp::LineShape sh = mp::line1d_tiled(p->g.n[0], sizeof(T) == 8, p->desc.n_iters,
+                                              p->desc.opts, phi ? 2 : 1, n_steps, &launches);
+    const mp::LineArgs<T> a = line_args<T>(p, c, G, osc_a);
+    T *cur[2] = {psi, phi}, *alt[2] = {(T *)p->L.psi_alt, phi ? (T *)p->L.tmp[0] : nullptr};
+    auto swap = [&]() {
+        for (int f = 0; f < 2; f++) {
+            T *t = cur[f];
+            cur[f] = alt[f];
+            alt[f] = t;
+        }
+    };
+    if (launches & 1) {
+        for (int f = 0; f < (phi ? 2 : 1); f++) {
+            hipError_t e = hipMemcpyAsync(alt[f], cur[f], sizeof(T) * cells_of(p->g),
+                                          hipMemcpyDeviceToDevice, p->stream);
+            if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
+        }
+        swap();
+    }
+    for (int l = 0; l < launches; l++) {
+        const int steps = n_steps / launches + (l < n_steps % launches ? 1 : 0);
+        bool tm = timer_begin(p, "k_resident1d");
+        hipError_t e = mp::line1d_launch<T>(sh, a, steps, cur[0], cur[1], alt[0], alt[1], p->stream);
+        if (tm) timer_end(p);
+        if (e != hipSuccess) return hip_fail(e, "1-D step launch");
+        swap();
+    }
+    return MPDATA_OK;
 }
 
 // Diagnostics of a step call's result (mpdata_set_step_diag): the final merge
@@ -377,8 +443,7 @@ int run_steps_polled(mpdata_plan *p, T *psi, const T *G, const T *c0, const T *c
         }
         hipError_t e;
         if (resident) {
-            e = mp::resident1d_steps<T>(p->g.n[0], p->g.bc[0], p->desc.n_iters, p->desc.opts,
-                                        cur, c0, G, n_steps, p->stream);
+            e = resident_steps<T>(p, cur, nullptr, c0, G, n_steps);
             if (e != hipSuccess) return hip_fail(e, "resident 1-D launch");
             done = n_steps;
         } else if (path == PATH_STAGED && p->desc.n_iters >= 2) {
@@ -420,14 +485,19 @@ int run_steps(mpdata_plan *p, T *psi, const T *G, const T *c0, const T *c1, cons
     if (p->cancel) return run_steps_polled<T>(p, psi, G, c0, c1, c2, n_steps);
     if (use_resident(p)) {
         bool tm = timer_begin(p, "k_resident1d");
-        hipError_t e = mp::resident1d_steps<T>(p->g.n[0], p->g.bc[0], p->desc.n_iters,
-                                               p->desc.opts, psi, c0, G, n_steps, p->stream);
+        hipError_t e = resident_steps<T>(p, psi, nullptr, c0, G, n_steps);
         if (tm) timer_end(p);
         if (e != hipSuccess) return hip_fail(e, "resident 1-D launch");
         p->steps_done = n_steps;
         return p->step_diag ? step_diag_finish<T>(p, psi, G, 0) : MPDATA_OK;
     }
     const int path = step_path(p);
+    if (path == PATH_LINE) {
+        int rc = line_steps<T>(p, psi, nullptr, c0, G, n_steps);
+        if (rc) return rc;
+        p->steps_done = n_steps;
+        return p->step_diag ? step_diag_finish<T>(p, psi, G, 0) : MPDATA_OK;
+    }
     if (path == PATH_STAGED && p->desc.n_iters >= 2) {
         // staged passes: psi^n is last read before the final corrective pass,
         // which reads only the previous pass's result, so the step may
@@ -757,18 +827,23 @@ int mpdata_osc_step(mpdata_plan *plan, void *psi, void *phi, const void *g, cons
         mp::resident1d_supported(plan->desc.n_dims, plan->g.n[0], f64, plan->desc.has_g, 1)) {
         // 1-D pair resident in LDS: every step of the call in one launch
         bool tm = timer_begin(plan, "k_resident1d");
-        hipError_t e =
-            f64 ? mp::resident1d_osc<double>(plan->g.n[0], plan->g.bc[0], plan->desc.n_iters,
-                                             plan->desc.opts, (double *)psi, (double *)phi,
-                                             (const double *)c0, (const double *)g, a, n_steps,
-                                             plan->stream)
-                : mp::resident1d_osc<float>(plan->g.n[0], plan->g.bc[0], plan->desc.n_iters,
-                                            plan->desc.opts, (float *)psi, (float *)phi,
-                                            (const float *)c0, (const float *)g, a, n_steps,
-                                            plan->stream);
+        hipError_t e = f64 ? resident_steps<double>(plan, (double *)psi, (double *)phi,
+                                                    (const double *)c0, (const double *)g,
+                                                    n_steps, a)
+                           : resident_steps<float>(plan, (float *)psi, (float *)phi,
+                                                   (const float *)c0, (const float *)g, n_steps,
+                                                   a);
         if (tm) timer_end(plan);
         return e == hipSuccess ? MPDATA_OK : hip_fail(e, "resident oscillator launch");
     }
+    // a longer 1-D pair: tiled launches of several steps (what mpdata_step
+    // refuses is left to it below)
+    if (step_path(plan) == PATH_LINE && !plan->cancel && !plan->step_diag && c0 && !c1 && !c2 &&
+        (g != nullptr) == (plan->desc.has_g != 0))
+        return f64 ? line_steps<double>(plan, (double *)psi, (double *)phi, (const double *)c0,
+                                        (const double *)g, n_steps, a)
+                   : line_steps<float>(plan, (float *)psi, (float *)phi, (const float *)c0,
+                                       (const float *)g, n_steps, a);
     for (int st = 0; st < n_steps; st++) {
         hipError_t e = f64 ? mp::osc_couple_launch<double>((double *)psi, (double *)phi, a, 0,
                                                            N, plan->stream)
@@ -1051,8 +1126,10 @@ struct AdjStepCtx {
 template <typename T> hipError_t adj_plain_step(void *ctx, const T *in, T *out)
 {
     const AdjStepCtx *x = (const AdjStepCtx *)ctx;
+    // (1-D: the stage kernels, which also record, so both give the same bits)
+    const int path = step_path(x->p);
     int rc = one_step<T>(x->p, in, out, (const T *)x->G, (const T *)x->c[0], (const T *)x->c[1],
-                         (const T *)x->c[2], step_path(x->p));
+                         (const T *)x->c[2], path == PATH_LINE ? PATH_STAGED : path);
     return rc == MPDATA_OK ? hipSuccess : hipErrorLaunchFailure;
 }
 

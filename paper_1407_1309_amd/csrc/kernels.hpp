@@ -16,6 +16,7 @@ namespace mp {
 struct Slots {
     int cus, per_cu;
 };
+// (kernel NULL: the number of units only)
 Slots slots_of(const void *kernel, int threads, size_t lds = 0);
 
 // Rows per chunk of a 2-D row march (one wave per strip and chunk) when the
@@ -201,16 +202,35 @@ hipError_t tlm_steps(const Geom &g, int n_iters, unsigned opts, T *psi, T *dpsi,
                      const T *const c[3], const T *const dc[3], int n_steps, void *ws,
                      hipStream_t s);
 
-// ---- 1-D grid resident in LDS: all steps of a call in one launch --------
-// two_fields: room for the oscillator pair (resident1d_osc)
+// ---- 1-D: many steps per launch (line1d.hpp) ------------------------------
+template <typename T> struct LineArgs {
+    int64_t n;
+    int bc, n_iters;
+    unsigned opts;
+    const T *c, *G;      // advector; G NULL: G == 1
+    double osc_a;        // coupling of the oscillator pair (phi given)
+};
+// A launch: K cells per lane, waves per workgroup, cells a workgroup makes
+// (n: the whole grid in one), recomputed cells on each side of a tile.
+constexpr int LINE_WAVES = 16;             // most waves of a workgroup
+struct LineShape {
+    int K, waves, tile, halo;
+};
+int line_radius(int n_iters, unsigned opts);   // cells a step depends on, each side
+int line_own(int radius, int K);               // cells of a wave without its halo
+// true for a grid that one workgroup advances by any number of steps in one
+// launch, in place (two_fields: the oscillator pair)
 bool resident1d_supported(int nd, int64_t n, int dtype_is_f64, int has_g, int two_fields = 0);
+LineShape line1d_whole(int64_t n, int n_iters, unsigned opts);
+// shape and number of launches for n_steps steps of a longer grid: an even
+// number, so that alternating between two buffers ends in the first, or one
+LineShape line1d_tiled(int64_t n, int f64, int n_iters, unsigned opts, int fields, int n_steps,
+                       int *launches);
+// one launch of `steps` steps of psi (and phi, the oscillator pair, or NULL);
+// psi_out may be psi only with the whole grid in one workgroup
 template <typename T>
-hipError_t resident1d_steps(int64_t n, int bc, int n_iters, unsigned opts, T *psi, const T *c,
-                            const T *G, int n_steps, hipStream_t s);
-// n_steps trapezoidal steps of the translating oscillator pair (psi, phi)
-template <typename T>
-hipError_t resident1d_osc(int64_t n, int bc, int n_iters, unsigned opts, T *psi, T *phi,
-                          const T *c, const T *G, double a, int n_steps, hipStream_t s);
+hipError_t line1d_launch(const LineShape &sh, const LineArgs<T> &a, int steps, const T *psi,
+                         const T *phi, T *psi_out, T *phi_out, hipStream_t s);
 
 // ---- batched fused 2-D: one launch over all tiles of all grids ---------
 struct BatchGrid {

@@ -454,12 +454,12 @@ Slots slots_of(const void *kernel, int threads, size_t lds)
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds) == hipSuccess) {
-        if (cus > 0) v.cus = cus;
-        if (per > 0) v.per_cu = per;
-    } else {
-        (void)hipGetLastError();
-    }
+        cus > 0)
+        v.cus = cus;
+    if (kernel && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds) ==
+                      hipSuccess && per > 0)
+        v.per_cu = per;
+    (void)hipGetLastError();
     return v;
 }
 
