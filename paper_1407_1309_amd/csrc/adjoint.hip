@@ -1846,7 +1846,7 @@ template <typename T> hipError_t adjoint_run(const AdjArgs<T> &a, hipStream_t s)
             e = hipMemcpyAsync(w.ck + (size_t)(st / ck) * N, cur, nb, hipMemcpyDeviceToDevice, s);
             if (e != hipSuccess) return e;
         }
-        if (st == a.n_steps - 1) break;   // the final state is not needed
+        if (st == (nck - 1) * ck) break;   // the last segment's states are recorded below
         e = a.plain_step ? a.plain_step(a.plain_ctx, cur, nxt) : record_step<T>(a, w, cur, nxt, s);
         if (e != hipSuccess) return e;
         T *t = cur;
