@@ -475,9 +475,20 @@ int run_steps_polled(mpdata_plan *p, T *psi, const T *G, const T *c0, const T *c
     return rc;
 }
 
+// steps that alternate between psi and the workspace's buffer: an odd number
+// of them starts from a copy there
+bool starts_from_copy(const mpdata_plan *p, int n_steps)
+{
+    if (p->cancel || use_resident(p) || !(n_steps & 1)) return false;
+    const int path = step_path(p);
+    return path != PATH_LINE && !(path == PATH_STAGED && p->desc.n_iters >= 2);
+}
+
+// r_pre: a_pre * r_pre is added to psi first, on the way into the copy (only
+// where starts_from_copy)
 template <typename T>
 int run_steps(mpdata_plan *p, T *psi, const T *G, const T *c0, const T *c1, const T *c2,
-              int n_steps)
+              int n_steps, const T *r_pre = nullptr, double a_pre = 0.0)
 {
     p->steps_done = 0;
     p->sdiag_ready = false;
@@ -513,8 +524,10 @@ int run_steps(mpdata_plan *p, T *psi, const T *G, const T *c0, const T *c1, cons
     T *alt = (T *)p->L.psi_alt;
     T *cur = psi, *nxt = alt;
     if (n_steps & 1) {
-        hipError_t e = hipMemcpyAsync(alt, psi, sizeof(T) * N, hipMemcpyDeviceToDevice, p->stream);
-        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
+        hipError_t e = r_pre ? mp::axpy_out_launch<T>(alt, psi, r_pre, a_pre, N, p->stream)
+                             : hipMemcpyAsync(alt, psi, sizeof(T) * N, hipMemcpyDeviceToDevice,
+                                              p->stream);
+        if (e != hipSuccess) return hip_fail(e, "copy into the workspace");
         cur = alt;
         nxt = psi;
     }
@@ -532,6 +545,32 @@ int run_steps(mpdata_plan *p, T *psi, const T *G, const T *c0, const T *c1, cons
     }
     p->steps_done = n_steps;
     return p->step_diag ? step_diag_finish<T>(p, psi, G, dparts) : MPDATA_OK;
+}
+
+// mpdata_step with an optional source term ahead of it (see run_steps)
+int checked_steps(mpdata_plan *plan, void *psi, const void *g, const void *c0, const void *c1,
+                  const void *c2, int n_steps, const void *r_pre, double a_pre)
+{
+    if (!plan) return fail(MPDATA_EINVAL, "plan is NULL");
+    if (plan->batched) return fail(MPDATA_EINVAL, "batched plan: use mpdata_step_batched");
+    if (!psi) return fail(MPDATA_EINVAL, "psi is NULL");
+    if (n_steps < 0) return fail(MPDATA_EINVAL, "n_steps < 0");
+    const void *c[3] = {c0, c1, c2};
+    for (int d = 0; d < 3; d++) {
+        if (d < plan->desc.n_dims && !c[d]) return fail(MPDATA_EINVAL, "c%d is NULL", d);
+        if (d >= plan->desc.n_dims && c[d])
+            return fail(MPDATA_EINVAL, "c%d given for a %d-D plan", d, plan->desc.n_dims);
+    }
+    if ((g != nullptr) != (plan->desc.has_g != 0))
+        return fail(MPDATA_EINVAL, plan->desc.has_g ? "plan has_g but g is NULL"
+                                                    : "g given but plan was made without has_g");
+    if (plan->desc.dtype == MPDATA_F64)
+        return run_steps<double>(plan, (double *)psi, (const double *)g, (const double *)c0,
+                                 (const double *)c1, (const double *)c2, n_steps,
+                                 (const double *)r_pre, a_pre);
+    return run_steps<float>(plan, (float *)psi, (const float *)g, (const float *)c0,
+                            (const float *)c1, (const float *)c2, n_steps, (const float *)r_pre,
+                            a_pre);
 }
 
 }  // namespace
@@ -736,24 +775,7 @@ int mpdata_step(mpdata_plan *plan, void *psi, const void *g, const void *c0, con
                 const void *c2, int n_steps)
 {
     TraceRange trace_range("mpdata_step");
-    if (!plan) return fail(MPDATA_EINVAL, "plan is NULL");
-    if (plan->batched) return fail(MPDATA_EINVAL, "batched plan: use mpdata_step_batched");
-    if (!psi) return fail(MPDATA_EINVAL, "psi is NULL");
-    if (n_steps < 0) return fail(MPDATA_EINVAL, "n_steps < 0");
-    const void *c[3] = {c0, c1, c2};
-    for (int d = 0; d < 3; d++) {
-        if (d < plan->desc.n_dims && !c[d]) return fail(MPDATA_EINVAL, "c%d is NULL", d);
-        if (d >= plan->desc.n_dims && c[d])
-            return fail(MPDATA_EINVAL, "c%d given for a %d-D plan", d, plan->desc.n_dims);
-    }
-    if ((g != nullptr) != (plan->desc.has_g != 0))
-        return fail(MPDATA_EINVAL, plan->desc.has_g ? "plan has_g but g is NULL"
-                                                    : "g given but plan was made without has_g");
-    if (plan->desc.dtype == MPDATA_F64)
-        return run_steps<double>(plan, (double *)psi, (const double *)g, (const double *)c0,
-                                 (const double *)c1, (const double *)c2, n_steps);
-    return run_steps<float>(plan, (float *)psi, (const float *)g, (const float *)c0,
-                            (const float *)c1, (const float *)c2, n_steps);
+    return checked_steps(plan, psi, g, c0, c1, c2, n_steps, nullptr, 0.0);
 }
 
 int mpdata_set_step_diag(mpdata_plan *plan, int on)
@@ -795,13 +817,16 @@ int mpdata_step_rhs(mpdata_plan *plan, void *psi, const void *g, const void *c0,
     const int64_t N = cells_of(plan->g);
     const bool f64 = plan->desc.dtype == MPDATA_F64;
     hipError_t e = hipSuccess;
-    if (r_pre)
+    // the term ahead of the step is added in place, or on the way into the
+    // workspace where the step starts from a copy
+    const bool in_copy = r_pre && starts_from_copy(plan, 1);
+    if (r_pre && !in_copy)
         e = f64 ? mp::axpy_launch<double>((double *)psi, (const double *)r_pre, a_pre, N,
                                           plan->stream)
                 : mp::axpy_launch<float>((float *)psi, (const float *)r_pre, a_pre, N,
                                          plan->stream);
     if (e != hipSuccess) return hip_fail(e, "source term launch");
-    int rc = mpdata_step(plan, psi, g, c0, c1, c2, 1);
+    int rc = checked_steps(plan, psi, g, c0, c1, c2, 1, in_copy ? r_pre : nullptr, a_pre);
     if (rc) return rc;
     if (r_post)
         e = f64 ? mp::axpy_launch<double>((double *)psi, (const double *)r_post, a_post, N,
@@ -935,6 +960,31 @@ int sw_run(mpdata_plan *plan, void *h, void *const q[3], void *h_prev, void *con
     const void *qc[3] = {qq[0], qq[1], qq[2]}, *qpc[3] = {qp[0], qp[1], qp[2]};
     double sp[3] = {1.0, 1.0, 1.0};
     for (int d = 0; d < nd; d++) sp[d] = dx[d];
+    // 2-D with the option sets the single pass saves for: one launch before
+    // the advection, one that advects the three fields and keeps level n as
+    // the previous one, one after it.  The advected copies live in cell
+    // fields of the workspace that the single pass of a two-pass step leaves
+    // free.
+    if (nd == 2 && plan->desc.n_iters == 2 && step_path(plan) == PATH_PASS2D &&
+        mp::pass2d_saves(plan->desc.opts)) {
+        T *hc = (T *)plan->L.bdn, *qs[2] = {(T *)plan->L.psi_alt, (T *)plan->L.bup};
+        double k[3] = {dt / dx[0], dt / dx[1], 0.0};
+        const mp::PassFields<T> fl{{hc, qs[0], qs[1]},
+                                   {(T *)h, qq[0], qq[1]},
+                                   {(T *)h_prev, qp[0], qp[1]}};
+        for (int st = 0; st < n_steps; st++) {
+            hipError_t e = mp::sw_pre2d_launch<T>(plan->g, (const T *)h, qq, (const T *)h_prev, qp,
+                                                  eps, k, grav, sp, dt, cc, hc, qs, plan->stream);
+            if (e == hipSuccess)
+                e = mp::pass2d_fields_launch<T>(plan->g, plan->desc.opts, 3, fl, cc[0], cc[1],
+                                                plan->tile_rows, plan->stream);
+            if (e == hipSuccess)
+                e = mp::sw_force_launch<T>(plan->g, (const T *)h, (T *)h_prev, qq, qp, grav, sp,
+                                           dt, 0, plan->stream);
+            if (e != hipSuccess) return hip_fail(e, "shallow-water launch");
+        }
+        return MPDATA_OK;
+    }
     for (int st = 0; st < n_steps; st++) {
         // advector at n+1/2 from levels n and n-1
         hipError_t e = vip_run<T>(plan, qc, h, qpc, h_prev, dt, sp, eps, c);

@@ -185,6 +185,32 @@ template <typename T>
 hipError_t pass2d_launch(const Geom &g, unsigned opts, const T *x, const T *c0, const T *c1,
                          const T *psi_n, const T *G, T *y, T *w0, T *w1, hipStream_t s,
                          const PassRecord<T> &rec = PassRecord<T>(), int tile_rows = 0);
+// the arguments of a pass (psi_n: psi^n, also with the donor pass folded in)
+// and its launch with (DONOR) and without it
+template <typename T> struct PassFields {
+    const T *x[3];
+    T *y[3];
+    T *save[3];          // y's old values go there (NULL: not kept)
+};
+template <typename T> struct PassArgs {
+    Geom g;
+    unsigned opts;
+    int fields;          // fields advected by the launch (more than one: y only, donor folded in)
+    PassFields<T> fl;
+    const T *c0, *c1, *psi_n, *G;
+    T *w0, *w1;
+    PassRecord<T> rec;
+    int tile_rows;
+    hipStream_t s;
+};
+template <typename T, bool DONOR> hipError_t pass2d_go(const PassArgs<T> &p);
+// the whole two-pass step of nf <= 3 fields x[] -> y[] under one advector in
+// one launch (G = 1), y's old values into save[]; for the option sets of
+// pass2d_saves
+bool pass2d_saves(unsigned opts);
+template <typename T>
+hipError_t pass2d_fields_launch(const Geom &g, unsigned opts, int nf, const PassFields<T> &fl,
+                                const T *c0, const T *c1, int tile_rows, hipStream_t s);
 // donor-cell pass of a 2-D grid, G = 1 (Kahan per opts); copy (optional)
 // receives x unchanged
 template <typename T>
@@ -253,6 +279,9 @@ int fused2d_strip_cols(int n_iters, unsigned opts);  // output columns per strip
 
 // ---- source terms and the oscillator coupling (rhs.hip) ----------------
 template <typename T> hipError_t axpy_launch(T *y, const T *x, double a, int64_t n, hipStream_t s);
+// out = y + a x (y kept)
+template <typename T>
+hipError_t axpy_out_launch(T *out, const T *y, const T *x, double a, int64_t n, hipStream_t s);
 template <typename T>
 hipError_t osc_couple_launch(T *psi, T *phi, double a, int implicit, int64_t n, hipStream_t s);
 
@@ -262,6 +291,14 @@ hipError_t osc_couple_launch(T *psi, T *phi, double a, int implicit, int64_t n, 
 template <typename T>
 hipError_t vip_launch(const Geom &g, const T *const num[3], const T *den, const T *const nump[3],
                       const T *denp, double eps, const double k[3], T *const c[3], hipStream_t s);
+// 2-D, one launch before the advection of a shallow-water step: the advector
+// of vip_launch (momenta q, depth h) and the fields to advect, hc = h and
+// qs[d] = q[d] + dt/2 (-grav h dh/dx_d)
+template <typename T>
+hipError_t sw_pre2d_launch(const Geom &g, const T *h, const T *const q[3], const T *hp,
+                           const T *const qp[3], double eps, const double k[3], double grav,
+                           const double dx[3], double dt, T *const c[3], T *hc, T *const qs[2],
+                           hipStream_t s);
 // q[d] += dt/2 * (-grav h dh/dx_d); with save, first q_prev[d] = q[d], h_prev = h
 template <typename T>
 hipError_t sw_force_launch(const Geom &g, const T *h, T *h_prev, T *const q[3],

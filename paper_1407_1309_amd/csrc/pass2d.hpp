@@ -1,5 +1,6 @@
-// pass2d.hip -- one corrective MPDATA pass on a 2-D grid in one launch, and
-// the 2-D donor-cell pass that precedes it.
+// pass2d.hpp -- one corrective MPDATA pass on a 2-D grid in one launch
+// (kernel templates; pass2d_f64_donor.hip and its siblings instantiate them,
+// pass2d.hip holds the dispatch and the donor-cell pass alone).
 //
 // For the 2-D configurations the whole-step fused kernel does not take (open
 // boundaries, iga, dfl, variable G, third-order terms): the pseudo-velocities
@@ -44,9 +45,8 @@ namespace {
 // n * r, r the hardware reciprocal refined by one Newton step, where it is in
 // range (FP64: r is a normal number; FP32: the divisor is normal or zero),
 // else the IEEE quotient -- lane by lane, so its value depends on its
-// operands only.  FP64 first tests the wave (no kept quotient out of range:
-// the fast forms only, no division issued).  Quotients not kept are
-// discarded by the caller.
+// operands only.  A wave with no kept quotient out of range (one test per
+// set) issues no division.  Quotients not kept are discarded by the caller.
 template <int K>
 __device__ __forceinline__ void lane_quotients(const double (&n)[K], const double (&d)[K],
                                                const bool (&keep)[K], double (&q)[K])
@@ -72,17 +72,21 @@ __device__ __forceinline__ void lane_quotients(const double (&n)[K], const doubl
 }
 template <int K>
 __device__ __forceinline__ void lane_quotients(const float (&n)[K], const float (&d)[K],
-                                               const bool (&)[K], float (&q)[K])
+                                               const bool (&keep)[K], float (&q)[K])
 {
+    bool in[K];
+    bool ok = true;
 #pragma unroll
     for (int k = 0; k < K; k++) {
-        if (__builtin_amdgcn_classf(d[k], 0x168)) {   // +-normal or +-zero
-            const float r = __builtin_amdgcn_rcpf(d[k]);
-            const float q0 = n[k] * r;
-            q[k] = fmaf(fmaf(-d[k], q0, n[k]), r, q0);
-        } else {
-            q[k] = n[k] / d[k];
-        }
+        in[k] = __builtin_amdgcn_classf(d[k], 0x168);   // +-normal or +-zero
+        ok = ok & (in[k] | !keep[k]);
+        const float r = __builtin_amdgcn_rcpf(d[k]);
+        const float q0 = n[k] * r;
+        q[k] = fmaf(fmaf(-d[k], q0, n[k]), r, q0);
+    }
+    if (__builtin_amdgcn_ballot_w64(!ok) != 0) {
+#pragma unroll
+        for (int k = 0; k < K; k++) q[k] = in[k] ? q[k] : n[k] / d[k];
     }
 }
 
@@ -198,21 +202,43 @@ template <bool TOT> constexpr int unroll() { return TOT ? 8 : 4; }
 // first chunks start at row 0 with the rows above filled with row 0.
 // HG: G is an array (loaded with the cell rows, row a at age CO); otherwise
 // G = 1.
-template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT> struct March {
+// VAR: what a launch may be asked for beside y (Variant): the plain and
+// divergent-flow ones write y only and the recording one the walls and
+// records, none with Kahan's summation; the general one decides it all at
+// run time.  Every run-time choice is a branch in every row, which splits
+// the row for the instruction scheduler and adds scalar work that a wave
+// issues in order: with the choices, the 64-bit row offsets formed by
+// multiplications and (FP32) a branch per quotient, a row of the FP64 iga +
+// limiter instance took 212 scalar beside 326 vector instructions.
+enum Variant { V_PLAIN = 0, V_DFL = 1, V_REC = 2, V_ANY = 3 };
+
+template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT, int VAR>
+struct March {
+    static constexpr bool OUT = VAR >= V_REC;      // w0, w1 and the records
+    // what y held before may be kept (the shallow-water fields' option sets:
+    // the previous time level, saved here instead of by a copy of its own)
+    static constexpr bool SAVE = DONOR && FCT && !HG && !TOT &&
+                                 ((IGA && VAR == V_DFL) || (ABS && VAR == V_PLAIN));
     static constexpr int CO = DONOR ? 1 : 0;   // age of row a in the c1 and G rings
     static constexpr int SH = TOT ? 1 : 0;     // row shift of the stages after V0
     static constexpr int XQ = TOT ? 8 : 4;     // x ring depth (ages 0..3+SH used)
     static constexpr int XR = TOT ? 4 : 2;     // right-neighbour ring (ages 0..1+SH)
     static constexpr int GQ = TOT ? 8 : 4;     // G ring (ages 0..CO+2+SH)
-    int n0, n1, i0, i1, bc0, rr, rw;   // rr: next cell row to load, rw: next wall row
-    int pr, pw;                        // rr, rw wrapped periodically (carried row to row)
-    int lane_lo, lane_hi;              // lanes of columns 0 and n1-1 (edge strips)
-    bool dfl, kahan, out_lane, w1_lane, fix_lo, fix_hi, prefill;
+    int n0, n1, i0, i1;
+    int rr, rw;                        // next cell row and wall row to load (periodic: wrapped)
+    int64_t oc, oc1, ow;               // their offsets in cell, c1 and c0 arrays (uniform)
+    int64_t ro, ro1;                   // a n1 and a (n1 + 1) of the current row a (uniform)
+    int lane_lo, lane_hi;              // lanes of columns 0 and n1-1 (edge strips; else 0)
+    bool fix, below, above;            // an edge strip; the lane lies outside an open domain
+    bool open0;                        // open along the rows
+    bool dfl, kahan, out_lane, w1_lane, prefill;
     int64_t ocol, ccol, wcol;          // per-lane column offsets
     const T *x, *pn, *c0, *c1, *G;
     T *y, *w0, *w1;
     T *v0r, *v1r, *bur, *bdr;          // records: raw velocities, coefficients
     T *xd;                             // record of the donor pass's result (DONOR)
+    T *save;                           // SAVE: receives y's old values, or NULL
+    T old;                             // SAVE: y's value of the next row to store
     T fx[PF], fp[PF], f0[PF], f1[PF], fg[PF];
     Ring<T, XQ> xq;
     Ring<T, 4> xl, c0q, c1q, mxq, mnq, pq;
@@ -220,37 +246,44 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
     Ring<T, XR> xr;
     Ring<T, 2> v0q, v1q, buq, bdq, aq0, aq1;
 
-    // x (or psi^n), psi^n, c1 and G of cell row r_cell and the dimension-0
-    // wall r_wall
-    __device__ __forceinline__ void fetch(int r_cell, int r_wall, T &vx, T &vp, T &v1, T &v0,
-                                          T &vg)
+    // x (or psi^n), psi^n, c1 and G of the next cell row and the next
+    // dimension-0 wall row; then both one row on (open: the edge row is read
+    // again outside the domain; periodic: wrapped at n0)
+    __device__ __forceinline__ void fetch(T &vx, T &vp, T &v1, T &v0, T &vg)
     {
-        fetch_at(map_cell(r_cell, n0, bc0), map_wall(r_wall, n0, bc0), vx, vp, v1, v0, vg);
-    }
-    // the same at mapped rows r (cell) and w (wall)
-    __device__ __forceinline__ void fetch_at(int64_t r, int64_t w, T &vx, T &vp, T &v1, T &v0,
-                                             T &vg)
-    {
-        vx = x[r * n1 + ccol];
-        if (FCT && !DONOR) vp = pn[r * n1 + ccol];
-        v1 = c1[r * (n1 + 1) + wcol];
-        v0 = c0[w * n1 + ccol];
-        if (HG) vg = G[r * n1 + ccol];
-    }
-
-    // rows rr / rw: open, clamped; periodic, the carried wrapped indices (a
-    // wrap test per row instead of a division)
-    __device__ __forceinline__ void load(int k)
-    {
-        const bool open = bc0 == BC_OPEN;
-        const int r = open ? min(max(rr, 0), n0 - 1) : pr;
-        const int w = open ? min(max(rw, 0), n0) : pw;
-        fetch_at(r, w, fx[k], fp[k], f1[k], f0[k], fg[k]);
+        vx = (x + oc)[ccol];
+        if (FCT && !DONOR) vp = (pn + oc)[ccol];
+        v1 = (c1 + oc1)[wcol];
+        v0 = (c0 + ow)[ccol];
+        if (HG) vg = (G + oc)[ccol];
         rr++;
         rw++;
-        pr = pr + 1 == n0 ? 0 : pr + 1;
-        pw = pw + 1 == n0 ? 0 : pw + 1;
+        const bool wr = !open0 && rr == n0, ww = !open0 && rw == n0;
+        const bool sr = !open0 || (rr >= 1 && rr < n0), sw = !open0 || (rw >= 1 && rw <= n0);
+        rr = wr ? 0 : rr;
+        rw = ww ? 0 : rw;
+        oc = wr ? 0 : oc + (sr ? n1 : 0);
+        oc1 = wr ? 0 : oc1 + (sr ? n1 + 1 : 0);
+        ow = ww ? 0 : ow + (sw ? n1 : 0);
     }
+    // the first row to load: cell row r and wall row w
+    __device__ __forceinline__ void seek(int r, int w)
+    {
+        const int bc = open0 ? BC_OPEN : BC_PERIODIC;
+        const int64_t mr = map_cell(r, n0, bc), mw = map_wall(w, n0, bc);
+        rr = open0 ? r : (int)mr;
+        rw = open0 ? w : (int)mw;
+        oc = mr * n1;
+        oc1 = mr * (n1 + 1);
+        ow = mw * n1;
+    }
+    __device__ __forceinline__ void load(int k) { fetch(fx[k], fp[k], f1[k], f0[k], fg[k]); }
+
+    __device__ __forceinline__ bool with_dfl() const
+    {
+        return VAR == V_DFL || (VAR == V_ANY && dfl);
+    }
+    __device__ __forceinline__ bool with_kahan() const { return VAR == V_ANY && kahan; }
 
     // G of cell row a - k (1 without HG)
     template <int P> __device__ __forceinline__ T g_row(int k) const
@@ -262,18 +295,20 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
     // donor result at a lane outside an open domain: the edge lane's
     __device__ __forceinline__ T edge_cols(T v)
     {
-        if (fix_lo) {
-            T e = lane_value(v, lane_lo);
-            if (lane < lane_lo) v = e;
-        }
-        if (fix_hi) {
-            T e = lane_value(v, lane_hi);
-            if (lane > lane_hi) v = e;
-        }
+        if (fix) v = edge_value(v);
         return v;
     }
+    __device__ __forceinline__ T edge_value(T v)
+    {
+        // (below / above: no lane where the strip does not have that edge)
+        const T lo = lane_value(v, lane_lo), hi = lane_value(v, lane_hi);
+        return below ? lo : (above ? hi : v);
+    }
 
-    template <int P> __device__ __forceinline__ void iter(int a)
+    // One row.  STAGE: 2, all of it; on the first rows of a chunk, above
+    // what any output row reads, 0: the pass input alone, 1: and the raw
+    // velocities.
+    template <int P, int STAGE> __device__ __forceinline__ void iter(int a)
     {
         constexpr int S = P % PF;
         T x_a, pn_a;
@@ -290,12 +325,12 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
             const T f0hi = upwind_fp(u0hi, pc, pp);
             const T f1lo = upwind_fp(u1, from_left(pc), pc);
             const T f1hi = from_right(f1lo);
-            x_a = edge_cols(donor_update_g<HG>(kahan, pc, f0hi - f0lo, f1hi - f1lo,
+            x_a = edge_cols(donor_update_g<HG>(with_kahan(), pc, f0hi - f0lo, f1hi - f1lo,
                                                g_row<P>(0)));
-            if (bc0 == BC_OPEN && a >= n0) x_a = AT(xq, XQ, 1);   // rows past the end
+            x_a = open0 && a >= n0 ? AT(xq, XQ, 1) : x_a;   // rows past the end
             pn_a = pc;
             // the donor result of the chunk's own rows and columns
-            if (xd && a >= i0 && a < i1 && out_lane) xd[(int64_t)a * n1 + ocol] = x_a;
+            if (OUT && xd && a >= i0 && a < i1 && out_lane) (xd + ro)[ocol] = x_a;
         } else {
             x_a = fx[S];
             pn_a = fp[S];
@@ -306,7 +341,7 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
         AT(xq, XQ, 0) = x_a;
         AT(xl, 4, 0) = from_left(x_a);
         AT(xr, XR, 0) = from_right(x_a);
-        if (DONOR && prefill) {
+        if (DONOR && P == 0 && prefill) {   // (a chunk's first row has phase 0)
             // first row of an open domain: the rows above are copies of it
             prefill = false;
 #pragma unroll
@@ -322,6 +357,16 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
                     AT(mnq, 4, k) = fmin(pn_a, x_a);
                 }
             }
+        }
+
+        if (FCT) {
+            AT(mxq, 4, 0) = fmax(pn_a, x_a);
+            AT(mnq, 4, 0) = fmin(pn_a, x_a);
+        }
+        if constexpr (STAGE == 0) {
+            ro += n1;
+            ro1 += n1 + 1;
+            return;
         }
 
         // psi-fractions: V0 at wall w = a - SH (rows w-1 | w), V1 of row a-1
@@ -410,7 +455,7 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
                 v0 = (fabs(u) - u * u) * fr[0];
                 v0 -= T(0.5) * u * cb * fr[1];
             }
-            if (dfl) {
+            if (with_dfl()) {
                 // mean of the divergences of the wall's two cells
                 const T c1a = AT(c1q, 4, CO + SH), c1b = AT(c1q, 4, CO + SH + 1);
                 T dv = (AT(c0q, 4, 1 + SH) - AT(c0q, 4, 2 + SH)) +
@@ -436,7 +481,7 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
                 v1 = (fabs(u) - u * u) * fr[2];
                 v1 -= T(0.5) * u * cb * fr[3];
             }
-            if (dfl) {
+            if (with_dfl()) {
                 // mean of the divergences of cells (a-1, j-1) and (a-1, j)
                 const T d0 = AT(c0q, 4, 1) - AT(c0q, 4, 2);
                 T dv = from_left(d0) + d0;
@@ -453,6 +498,11 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
         }
         AT(v0q, 2, 0) = v0;
         if constexpr (TOT) AT(v1q, 2, 0) = v1;
+        if constexpr (STAGE == 1) {
+            ro += n1;
+            ro1 += n1 + 1;
+            return;
+        }
         // V1 of the limiter's row rl = a-1-SH
         const T v1l = TOT ? AT(v1q, 2, 1) : v1;
         const int rl = a - 1 - SH;
@@ -460,8 +510,6 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
         T lim0, lim1;
         if (FCT) {
             // bounds over {psi^n, x} at the cell and its face neighbours
-            AT(mxq, 4, 0) = fmax(pn_a, x_a);
-            AT(mnq, 4, 0) = fmin(pn_a, x_a);
             const T m1 = AT(mxq, 4, SH + 1), n1v = AT(mnq, 4, SH + 1);
             const T mx = fmax(fmax(m1, fmax(AT(mxq, 4, SH + 2), AT(mxq, 4, SH))),
                               fmax(from_left(m1), from_right(m1)));
@@ -489,19 +537,9 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
             T bd = fout > T(0) ? bq[1] : T(1);
             // open columns: a cell left of column 0 / right of column n1-1
             // has the edge cell's coefficients
-            if (fix_lo) {
-                T eu = lane_value(bu, lane_lo), ed = lane_value(bd, lane_lo);
-                if (lane < lane_lo) {
-                    bu = eu;
-                    bd = ed;
-                }
-            }
-            if (fix_hi) {
-                T eu = lane_value(bu, lane_hi), ed = lane_value(bd, lane_hi);
-                if (lane > lane_hi) {
-                    bu = eu;
-                    bd = ed;
-                }
+            if (fix) {
+                bu = edge_value(bu);
+                bd = edge_value(bd);
             }
             AT(buq, 2, 0) = bu;
             AT(bdq, 2, 0) = bd;
@@ -516,11 +554,11 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
             {
                 T bu_l = AT(buq, 2, 1), bd_l = AT(bdq, 2, 1);
                 T bu_r = AT(buq, 2, 0), bd_r = AT(bdq, 2, 0);
-                if (bc0 == BC_OPEN) {
+                if (open0 && (rl == 0 || rl == n0)) {
                     if (rl == 0) {
                         bu_l = bu_r;
                         bd_l = bd_r;
-                    } else if (rl == n0) {
+                    } else {
                         bu_r = bu_l;
                         bd_r = bd_l;
                     }
@@ -539,21 +577,22 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
 
         // limited velocities for a following pass (and, when asked, the raw
         // velocities and the coefficients): wall rl and row rl
-        if (w0) {
+        if (OUT && w0) {
             const int w = rl;
-            if (w >= i0 && (w < i1 || (w == n0 && i1 == n0 && bc0 == BC_OPEN))) {
-                const int64_t k0 = (int64_t)w * n1 + ocol, k1 = (int64_t)w * (n1 + 1) + ocol;
+            if (w >= i0 && (w < i1 || (w == n0 && i1 == n0 && open0))) {
+                const int64_t k0 = ro - (int64_t)(1 + SH) * n1;
+                const int64_t k1 = ro1 - (int64_t)(1 + SH) * (n1 + 1);
                 if (out_lane) {
-                    w0[k0] = lim0;
-                    if (v0r) v0r[k0] = AT(v0q, 2, 1);
+                    (w0 + k0)[ocol] = lim0;
+                    if (v0r) (v0r + k0)[ocol] = AT(v0q, 2, 1);
+                    if (FCT && bur && w < i1) {
+                        (bur + k0)[ocol] = AT(buq, 2, 0);
+                        (bdr + k0)[ocol] = AT(bdq, 2, 0);
+                    }
                 }
                 if (w < i1 && w1_lane) {
-                    w1[k1] = lim1;
-                    if (v1r) v1r[k1] = v1l;
-                }
-                if (FCT && bur && w < i1 && out_lane) {
-                    bur[k0] = AT(buq, 2, 0);
-                    bdr[k0] = AT(bdq, 2, 0);
+                    (w1 + k1)[ocol] = lim1;
+                    if (v1r) (v1r + k1)[ocol] = v1l;
                 }
             }
         }
@@ -572,51 +611,83 @@ template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TO
             f1lo = pos(AT(aq1, 2, 1)) * AT(xl, 4, SH + 2) + neg(AT(aq1, 2, 1)) * xc;
         }
         const T f1hi = from_right(f1lo);
-        const T res = donor_update_g<HG>(kahan, xc, f0hi - f0lo, f1hi - f1lo, g_row<P>(2 + SH));
+        const T res =
+            donor_update_g<HG>(with_kahan(), xc, f0hi - f0lo, f1hi - f1lo, g_row<P>(2 + SH));
         const int r = rl - 1;
-        if (y && r >= i0 && r < i1 && out_lane) y[(int64_t)r * n1 + ocol] = res;
+        if constexpr (SAVE) {
+            if (save) {
+                // the old value of row r arrived with the previous row
+                const T was = old;
+                const int next = min(max(r + 1, i0), i1 - 1);
+                old = (y + (int64_t)next * n1)[ccol];
+                if (r >= i0 && r < i1 && out_lane) (save + ro - (int64_t)(2 + SH) * n1)[ocol] = was;
+            }
+        }
+        if ((!OUT || y) && r >= i0 && r < i1 && out_lane) (y + ro - (int64_t)(2 + SH) * n1)[ocol] = res;
+        ro += n1;
+        ro1 += n1 + 1;
     }
-    int lane;
 };
 
-template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT, int P = 0>
-__device__ __forceinline__ void iter_block(March<T, FCT, IGA, ABS, DONOR, HG, TOT> &m, int a)
+// N rows from row a on, with phases P0 ..
+template <int N, int P0, typename M, int I = 0>
+__device__ __forceinline__ void iter_block(M &m, int a)
 {
-    if constexpr (P < unroll<TOT>()) {
-        m.template iter<P>(a + P);
-        iter_block<T, FCT, IGA, ABS, DONOR, HG, TOT, P + 1>(m, a);
+    if constexpr (I < N) {
+        m.template iter<P0 + I, 2>(a + I);
+        iter_block<N, P0, M, I + 1>(m, a);
+    }
+}
+
+// The first LEAD rows of a chunk whose first output row is i0 = a + 3: the
+// rows i0-3, i0-2 (TOT: and i0-1) feed the rings only, the next one the raw
+// velocities (V0 at wall i0-1, V1 of the limiter's first row), and from
+// then on every stage counts.
+constexpr int LEAD = 4;
+constexpr double LEAD_COST = 2.0;   // in whole rows
+template <typename M> __device__ __forceinline__ void lead_in(M &m, int a)
+{
+    m.template iter<0, 0>(a);
+    m.template iter<1, 0>(a + 1);
+    if constexpr (M::SH) {
+        m.template iter<2, 0>(a + 2);
+        m.template iter<3, 1>(a + 3);
+    } else {
+        m.template iter<2, 1>(a + 2);
+        m.template iter<3, 2>(a + 3);
     }
 }
 
 // DONOR: x is psi^n (the donor pass is done here); otherwise x is the
 // previous pass's result and psi_n is psi^n.
-template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT>
+template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT, int VAR>
 __global__ void __launch_bounds__(WAVE)
     k_pass2d(int n0, int n1, int bc0, int bc1, int th, int strips, int dfl, int kahan,
-             const T *__restrict__ x, const T *__restrict__ c0, const T *__restrict__ c1,
-             const T *__restrict__ psi_n, const T *__restrict__ G, T *__restrict__ y,
-             T *__restrict__ w0,
+             PassFields<T> fl, const T *__restrict__ c0, const T *__restrict__ c1,
+             const T *__restrict__ psi_n, const T *__restrict__ G, T *__restrict__ w0,
              T *__restrict__ w1, T *__restrict__ v0r, T *__restrict__ v1r,
              T *__restrict__ bur, T *__restrict__ bdr, T *__restrict__ xd)
 {
     constexpr int HL = Lanes<DONOR, TOT>::HL, HR = Lanes<DONOR, TOT>::HR;
     constexpr int OW = Lanes<DONOR, TOT>::OW;
-    const int b = blockIdx.x;
-    const int strip = b % strips, chunk = b / strips;
+    const int strip = blockIdx.x % strips, chunk = blockIdx.x / strips;
     const int i0 = chunk * th;
     const int i1 = i0 + th < n0 ? i0 + th : n0;
     const int jstrip0 = strip * OW;
+    // several fields under one advector: one after another along the grid
+    const T *x = fl.x[blockIdx.y];
+    T *y = fl.y[blockIdx.y];
+    if (DONOR) psi_n = x;   // (so that the fields of a launch are alike)
     const int lane = threadIdx.x & (WAVE - 1);
     const int col = jstrip0 - HL + lane;
 
-    using M = March<T, FCT, IGA, ABS, DONOR, HG, TOT>;
+    using M = March<T, FCT, IGA, ABS, DONOR, HG, TOT, VAR>;
     M m;
     m.n0 = n0;
     m.n1 = n1;
     m.i0 = i0;
     m.i1 = i1;
-    m.bc0 = bc0;
-    m.lane = lane;
+    m.open0 = bc0 == BC_OPEN;
     m.dfl = dfl != 0;
     m.kahan = kahan != 0;
     m.x = x;
@@ -632,6 +703,10 @@ __global__ void __launch_bounds__(WAVE)
     m.bur = bur;
     m.bdr = bdr;
     m.xd = DONOR ? xd : nullptr;
+    if constexpr (M::SAVE) {
+        m.save = fl.save[blockIdx.y];
+        m.old = T(0);
+    }
     m.ccol = map_cell(col, n1, bc1);
     m.wcol = map_wall(col, n1, bc1);
     m.ocol = col;
@@ -640,10 +715,13 @@ __global__ void __launch_bounds__(WAVE)
     // columns, plus the edge wall n1 (open) by the last strip
     m.w1_lane = (lane >= HL && lane < WAVE - HR && col >= 0 && col < n1) ||
                 (bc1 == BC_OPEN && col == n1 && strip == strips - 1);
-    m.lane_lo = HL - jstrip0;
-    m.lane_hi = n1 - 1 - jstrip0 + HL;
-    m.fix_lo = bc1 == BC_OPEN && jstrip0 - HL < 0;
-    m.fix_hi = bc1 == BC_OPEN && jstrip0 - HL + WAVE > n1;
+    const bool lo = bc1 == BC_OPEN && jstrip0 - HL < 0;
+    const bool hi = bc1 == BC_OPEN && jstrip0 - HL + WAVE > n1;
+    m.lane_lo = lo ? HL - jstrip0 : 0;
+    m.lane_hi = hi ? n1 - 1 - jstrip0 + HL : 0;
+    m.fix = lo || hi;
+    m.below = lo && lane < m.lane_lo;
+    m.above = hi && lane > m.lane_hi;
     m.xq.zero();
     m.xl.zero();
     m.c0q.zero();
@@ -675,150 +753,84 @@ __global__ void __launch_bounds__(WAVE)
     m.prefill = DONOR && bc0 == BC_OPEN && i0 < 3;
     const int a_begin = m.prefill ? 0 : i0 - 3;
     const int a_end = i1 + 1 + M::SH;
+    m.ro = (int64_t)a_begin * n1;
+    m.ro1 = (int64_t)a_begin * (n1 + 1);
     if (DONOR) {
         T vp;
-        m.fetch(a_begin - 1, a_begin - 1, m.pq.v[slot<4>(0, 2)], vp, m.c1q.v[slot<4>(0, 2)],
-                m.c0q.v[slot<4>(0, 2)], m.gq.v[slot<M::GQ>(0, 2)]);
-        m.fetch(a_begin, a_begin, m.pq.v[slot<4>(0, 1)], vp, m.c1q.v[slot<4>(0, 1)],
-                m.c0q.v[slot<4>(0, 1)], m.gq.v[slot<M::GQ>(0, 1)]);
-        m.rr = a_begin + 1;
-        m.rw = a_begin + 1;
+        m.seek(a_begin - 1, a_begin - 1);
+        m.fetch(m.pq.v[slot<4>(0, 2)], vp, m.c1q.v[slot<4>(0, 2)], m.c0q.v[slot<4>(0, 2)],
+                m.gq.v[slot<M::GQ>(0, 2)]);
+        m.fetch(m.pq.v[slot<4>(0, 1)], vp, m.c1q.v[slot<4>(0, 1)], m.c0q.v[slot<4>(0, 1)],
+                m.gq.v[slot<M::GQ>(0, 1)]);
     } else {
-        m.rr = a_begin;
-        m.rw = a_begin + 1;
+        m.seek(a_begin, a_begin + 1);
     }
-    m.pr = (int)map_cell(m.rr, n0, BC_PERIODIC);
-    m.pw = (int)map_cell(m.rw, n0, BC_PERIODIC);
 #pragma unroll
     for (int k = 0; k < PF; k++) m.load(k);
-    for (int a = a_begin; a <= a_end; a += unroll<TOT>())
-        iter_block<T, FCT, IGA, ABS, DONOR, HG, TOT>(m, a);
+    constexpr int U = unroll<TOT>();
+    if (m.prefill) {
+        for (int a = a_begin; a <= a_end; a += U) iter_block<U, 0>(m, a);
+        return;
+    }
+    lead_in(m, a_begin);
+    for (int a = a_begin + LEAD; a <= a_end; a += U) iter_block<U, LEAD>(m, a);
 }
 
-// Donor-cell pass of a 2-D grid (eqs. upstream, F; G = 1): one thread per
-// cell, a block of 256 threads per row segment (the row is wave-uniform, so
-// no division per thread).  With `copy`, psi^n is also written there (for
-// an in-place step whose corrective passes still need psi^n).
-constexpr int DB = 256;
-
-template <typename T>
-__global__ void __launch_bounds__(DB)
-    k_donor2d(int n0, int n1, int bc0, int bc1, int bpr, int kahan, const T *__restrict__ x,
-              const T *__restrict__ c0, const T *__restrict__ c1, T *__restrict__ out,
-              T *__restrict__ copy)
+template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT, int VAR>
+hipError_t launch(const PassArgs<T> &p)
 {
-    const int row = blockIdx.x / bpr;
-    const int j = (blockIdx.x - row * bpr) * DB + threadIdx.x;
-    if (j >= n1) return;
-    const int64_t r = (int64_t)row * n1;
-    const int64_t rm = (int64_t)wrap_cell(row - 1, n0, bc0) * n1;
-    const int64_t rp = (int64_t)wrap_cell(row + 1, n0, bc0) * n1;
-    const int jm = wrap_cell(j - 1, n1, bc1), jp = wrap_cell(j + 1, n1, bc1);
-    const T xc = x[r + j];
-    const T u0lo = c0[r + j];
-    const T u0hi = c0[(int64_t)wrap_wall(row + 1, n0, bc0) * n1 + j];
-    const int64_t r1 = (int64_t)row * (n1 + 1);
-    const T u1lo = c1[r1 + j];
-    const T u1hi = c1[r1 + wrap_wall(j + 1, n1, bc1)];
-    const T f0lo = upwind_fp(u0lo, x[rm + j], xc);
-    const T f0hi = upwind_fp(u0hi, xc, x[rp + j]);
-    const T f1lo = upwind_fp(u1lo, x[r + jm], xc);
-    const T f1hi = upwind_fp(u1hi, xc, x[r + jp]);
-    out[r + j] = donor_update(kahan != 0, xc, f0hi - f0lo, f1hi - f1lo);
-    if (copy) copy[r + j] = xc;
-}
-
-template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT>
-hipError_t launch(const Geom &g, unsigned opts, const T *x, const T *c0, const T *c1,
-                  const T *psi_n, const T *G, T *y, T *w0, T *w1, const PassRecord<T> &rec,
-                  int tile_rows, hipStream_t s)
-{
-    const int64_t n0 = g.n[0], n1 = g.n[1];
+    const int64_t n0 = p.g.n[0], n1 = p.g.n[1];
     const int64_t strips = cdiv(n1, Lanes<DONOR, TOT>::OW);
-    auto kern = k_pass2d<T, FCT, IGA, ABS, DONOR, HG, TOT>;
-    int64_t th = tile_rows;
+    auto kern = k_pass2d<T, FCT, IGA, ABS, DONOR, HG, TOT, VAR>;
+    int64_t th = p.tile_rows;
     if (th <= 0) {
-        // a chunk runs th + 5 iterations (one more under TOT)
+        // a chunk runs th + 5 iterations (one more under TOT), of which the
+        // first LEAD do part of the work
         static const Slots slots = slots_of((const void *)kern, WAVE);
-        th = march_rows(n0, strips, slots, TOT ? 6 : 5, unroll<TOT>(), 1);
+        th = march_rows(n0, strips * p.fields, slots, TOT ? 2 : 1, unroll<TOT>(), 1, LEAD_COST);
     }
     if (th > n0) th = n0;
-    const int64_t blocks = strips * cdiv(n0, th);
-    kern<<<(unsigned)blocks, WAVE, 0, s>>>(
-        (int)n0, (int)n1, g.bc[0], g.bc[1], (int)th, (int)strips, (opts & OPT_DFL) ? 1 : 0,
-        (opts & OPT_KAHAN) ? 1 : 0, x, c0, c1, psi_n, G, y, w0, w1, rec.v0, rec.v1, rec.bu,
-        rec.bd, rec.xd);
+    const dim3 blocks((unsigned)(strips * cdiv(n0, th)), (unsigned)p.fields);
+    kern<<<blocks, WAVE, 0, p.s>>>(
+        (int)n0, (int)n1, p.g.bc[0], p.g.bc[1], (int)th, (int)strips, (p.opts & OPT_DFL) ? 1 : 0,
+        (p.opts & OPT_KAHAN) ? 1 : 0, p.fl, p.c0, p.c1, p.psi_n, p.G, p.w0, p.w1, p.rec.v0,
+        p.rec.v1, p.rec.bu, p.rec.bd, p.rec.xd);
     return hipGetLastError();
 }
 
 }  // namespace
 
-bool pass2d_supported(int nd, int n_iters, unsigned opts, int has_g, const int64_t n[3])
+// The instance of a launch.  The variants without run-time choices exist for
+// what steps and recordings ask for: y alone (every option), y with the
+// divergent-flow term under iga and the limiter (shallow water), and the
+// walls and records without iga or abs; everything else is V_ANY.
+template <typename T, bool DONOR> hipError_t pass2d_go(const PassArgs<T> &p)
 {
-    (void)has_g;   // G = 1 and variable G alike
-    if (nd != 2 || n_iters < 2) return false;
-    if ((opts & OPT_ABS) && (opts & OPT_IGA)) return false;
-    // 32-bit row / column arithmetic
-    return n[0] < (1 << 30) && n[1] < (1 << 30) && n[0] * (n[1] + 1) < ((int64_t)1 << 31);
-}
-
-template <typename T>
-hipError_t pass2d_launch(const Geom &g, unsigned opts, const T *x, const T *c0, const T *c1,
-                         const T *psi_n, const T *G, T *y, T *w0, T *w1, hipStream_t s,
-                         const PassRecord<T> &rec, int tile_rows)
-{
-    const bool fct = opts & OPT_FCT, iga = opts & OPT_IGA, absf = opts & OPT_ABS;
-    // psi_n NULL: the first corrective pass with the donor pass folded in
-    // (x = psi^n)
-    const bool donor = psi_n == nullptr;
-    const T *pn = donor ? x : psi_n;
-    const bool tot = opts & OPT_TOT;
-    auto go = [&](auto F, auto I, auto A, auto D, auto H, auto O) {
-        return launch<T, decltype(F)::value, decltype(I)::value, decltype(A)::value,
-                      decltype(D)::value, decltype(H)::value, decltype(O)::value>(
-            g, opts, x, c0, c1, pn, G, y, w0, w1, rec, tile_rows, s);
+    const bool fct = p.opts & OPT_FCT, iga = p.opts & OPT_IGA, absf = p.opts & OPT_ABS;
+    const bool tot = p.opts & OPT_TOT, dfl = p.opts & OPT_DFL, kahan = p.opts & OPT_KAHAN;
+    const bool out = p.w0 || p.rec.xd || p.rec.v0 || p.rec.bu || !p.fl.y[0];
+    auto by_v = [&](auto F, auto I, auto A, auto H, auto O) {
+        constexpr bool f = decltype(F)::value, i = decltype(I)::value, a = decltype(A)::value;
+        constexpr bool h = decltype(H)::value, o = decltype(O)::value;
+        if (!kahan && !dfl && !out) return launch<T, f, i, a, DONOR, h, o, V_PLAIN>(p);
+        if constexpr (f && i && !h && !o)
+            if (!kahan && !out) return launch<T, f, i, a, DONOR, h, o, V_DFL>(p);
+        if constexpr (!i && !a)
+            if (!kahan && !dfl) return launch<T, f, i, a, DONOR, h, o, V_REC>(p);
+        return launch<T, f, i, a, DONOR, h, o, V_ANY>(p);
     };
     using TT = std::true_type;
     using FF = std::false_type;
-    auto by_t = [&](auto F, auto I, auto A, auto D, auto H) {
-        return tot ? go(F, I, A, D, H, TT{}) : go(F, I, A, D, H, FF{});
+    auto by_t = [&](auto F, auto I, auto A, auto H) {
+        return tot ? by_v(F, I, A, H, TT{}) : by_v(F, I, A, H, FF{});
     };
-    auto by_g = [&](auto F, auto I, auto A, auto D) {
-        return G ? by_t(F, I, A, D, TT{}) : by_t(F, I, A, D, FF{});
+    auto by_g = [&](auto F, auto I, auto A) {
+        return p.G ? by_t(F, I, A, TT{}) : by_t(F, I, A, FF{});
     };
-    auto by_d = [&](auto F, auto I, auto A) {
-        return donor ? by_g(F, I, A, TT{}) : by_g(F, I, A, FF{});
-    };
-    auto by_f = [&](auto I, auto A) { return fct ? by_d(TT{}, I, A) : by_d(FF{}, I, A); };
+    auto by_f = [&](auto I, auto A) { return fct ? by_g(TT{}, I, A) : by_g(FF{}, I, A); };
     if (iga) return by_f(TT{}, FF{});
     if (absf) return by_f(FF{}, TT{});
     return by_f(FF{}, FF{});
 }
-
-template <typename T>
-hipError_t donor2d_launch(const Geom &g, unsigned opts, const T *x, const T *c0, const T *c1,
-                          T *out, T *copy, hipStream_t s)
-{
-    const int bpr = (int)cdiv(g.n[1], DB);
-    k_donor2d<T><<<(unsigned)(bpr * g.n[0]), DB, 0, s>>>((int)g.n[0], (int)g.n[1], g.bc[0],
-                                                         g.bc[1], bpr,
-                                                         (opts & OPT_KAHAN) ? 1 : 0, x, c0, c1,
-                                                         out, copy);
-    return hipGetLastError();
-}
-
-template hipError_t donor2d_launch<float>(const Geom &, unsigned, const float *, const float *,
-                                          const float *, float *, float *, hipStream_t);
-template hipError_t donor2d_launch<double>(const Geom &, unsigned, const double *,
-                                           const double *, const double *, double *, double *,
-                                           hipStream_t);
-template hipError_t pass2d_launch<float>(const Geom &, unsigned, const float *, const float *,
-                                         const float *, const float *, const float *, float *,
-                                         float *, float *, hipStream_t, const PassRecord<float> &,
-                                         int);
-template hipError_t pass2d_launch<double>(const Geom &, unsigned, const double *, const double *,
-                                          const double *, const double *, const double *,
-                                          double *, double *, double *, hipStream_t,
-                                          const PassRecord<double> &, int);
 
 }  // namespace mp

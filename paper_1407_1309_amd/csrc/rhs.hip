@@ -17,6 +17,15 @@ template <typename T> __global__ void k_axpy(T *y, const T *__restrict__ x, T a,
         y[i] += a * x[i];
 }
 
+// out = y + a x: a source term added on the way into the workspace
+template <typename T>
+__global__ void k_axpy_out(T *__restrict__ out, const T *__restrict__ y, const T *__restrict__ x,
+                           T a, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * EB + threadIdx.x; i < n; i += (int64_t)gridDim.x * EB)
+        out[i] = y[i] + a * x[i];
+}
+
 // explicit half of the coupling: (psi, phi) <- (psi + a phi, phi - a psi)
 template <typename T> __global__ void k_osc_explicit(T *psi, T *phi, T a, int64_t n)
 {
@@ -55,6 +64,13 @@ template <typename T> hipError_t axpy_launch(T *y, const T *x, double a, int64_t
 }
 
 template <typename T>
+hipError_t axpy_out_launch(T *out, const T *y, const T *x, double a, int64_t n, hipStream_t s)
+{
+    k_axpy_out<T><<<grid_for(n), EB, 0, s>>>(out, y, x, (T)a, n);
+    return hipGetLastError();
+}
+
+template <typename T>
 hipError_t osc_couple_launch(T *psi, T *phi, double a, int implicit, int64_t n, hipStream_t s)
 {
     if (implicit)
@@ -66,6 +82,10 @@ hipError_t osc_couple_launch(T *psi, T *phi, double a, int implicit, int64_t n, 
 
 template hipError_t axpy_launch<float>(float *, const float *, double, int64_t, hipStream_t);
 template hipError_t axpy_launch<double>(double *, const double *, double, int64_t, hipStream_t);
+template hipError_t axpy_out_launch<float>(float *, const float *, const float *, double, int64_t,
+                                           hipStream_t);
+template hipError_t axpy_out_launch<double>(double *, const double *, const double *, double,
+                                            int64_t, hipStream_t);
 template hipError_t osc_couple_launch<float>(float *, float *, double, int, int64_t, hipStream_t);
 template hipError_t osc_couple_launch<double>(double *, double *, double, int, int64_t,
                                               hipStream_t);

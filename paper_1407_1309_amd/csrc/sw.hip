@@ -114,6 +114,73 @@ __global__ void k_sw_force1(Geom g, int d, const T *__restrict__ h, T *__restric
     }
 }
 
+// 2-D, one thread per cell of a row (blockIdx.y: the row, so no division of
+// a flat index): everything that precedes the advection of a shallow-water
+// step.  The advector at the cell's low walls (and by the last row and
+// column at the far edge walls) with k_vip's expressions, and the fields to
+// advect: the depth copied, the momenta with the explicit half of the
+// forcing (k_sw_force1's expressions).  Bound by memory: levels n and n-1 of
+// three fields in, the advector and three fields out (88 bytes a cell in
+// FP64), where k_vip per dimension and k_sw_force1 per component read them
+// three times over.  1024^2 FP64: 38 us in four launches before.
+template <typename T>
+__global__ void __launch_bounds__(SB)
+    k_sw_pre2d(int n0, int n1, int bc0, int bc1, const T *__restrict__ h,
+               const T *__restrict__ q0, const T *__restrict__ q1, const T *__restrict__ hp,
+               const T *__restrict__ qp0, const T *__restrict__ qp1, T eps, T k0, T k1, T ngrav,
+               T tdx0, T tdx1, T half_dt, T *__restrict__ c0, T *__restrict__ c1,
+               T *__restrict__ hc, T *__restrict__ qs0, T *__restrict__ qs1)
+{
+    const int j = blockIdx.x * SB + threadIdx.x;
+    if (j >= n1) return;
+    for (int i = blockIdx.y; i < n0; i += gridDim.y) {
+        const int64_t t = (int64_t)i * n1 + j;
+        const int64_t up = (int64_t)wrap_cell(i - 1, n0, bc0) * n1 + j;
+        const int64_t dn = (int64_t)wrap_cell(i + 1, n0, bc0) * n1 + j;
+        const int64_t lf = (int64_t)i * n1 + wrap_cell(j - 1, n1, bc1);
+        const int64_t rt = (int64_t)i * n1 + wrap_cell(j + 1, n1, bc1);
+        auto vext = [&](const T *q, const T *qp, int64_t m) {
+            return T(1.5) * vel(q, h, m, eps) - T(0.5) * vel(qp, hp, m, eps);
+        };
+        const T u0 = vext(q0, qp0, t), u1 = vext(q1, qp1, t);
+        c0[t] = k0 * (T(0.5) * (vext(q0, qp0, up) + u0));
+        c1[t + i] = k1 * (T(0.5) * (vext(q1, qp1, lf) + u1));
+        if (i == n0 - 1) c0[t + n1] = k0 * (T(0.5) * (u0 + vext(q0, qp0, dn)));
+        if (j == n1 - 1) c1[t + i + 1] = k1 * (T(0.5) * (u1 + vext(q1, qp1, rt)));
+        const T hm = h[t];
+        hc[t] = hm;
+        const T f0 = ngrav * hm * (h[dn] - h[up]) / tdx0;
+        const T f1 = ngrav * hm * (h[rt] - h[lf]) / tdx1;
+        qs0[t] = q0[t] + half_dt * f0;
+        qs1[t] = q1[t] + half_dt * f1;
+    }
+}
+
+// 2-D, the forcing after the advection (k_sw_force without the save)
+template <typename T>
+__global__ void __launch_bounds__(SB)
+    k_sw_force2d(int n0, int n1, int bc0, int bc1, const T *__restrict__ h, T *__restrict__ q0,
+                 T *__restrict__ q1, T ngrav, T tdx0, T tdx1, T half_dt)
+{
+    const int j = blockIdx.x * SB + threadIdx.x;
+    if (j >= n1) return;
+    for (int i = blockIdx.y; i < n0; i += gridDim.y) {
+        const int64_t t = (int64_t)i * n1 + j;
+        const T hm = h[t];
+        const T f0 = ngrav * hm * (h[(int64_t)wrap_cell(i + 1, n0, bc0) * n1 + j] -
+                                   h[(int64_t)wrap_cell(i - 1, n0, bc0) * n1 + j]) / tdx0;
+        const T f1 = ngrav * hm * (h[(int64_t)i * n1 + wrap_cell(j + 1, n1, bc1)] -
+                                   h[(int64_t)i * n1 + wrap_cell(j - 1, n1, bc1)]) / tdx1;
+        q0[t] = q0[t] + half_dt * f0;
+        q1[t] = q1[t] + half_dt * f1;
+    }
+}
+
+dim3 grid2d(const Geom &g)
+{
+    return dim3((unsigned)cdiv(g.n[1], SB), (unsigned)(g.n[0] < 65535 ? g.n[0] : 65535));
+}
+
 unsigned blocks_for(int64_t n)
 {
     int64_t b = cdiv(n, SB);
@@ -143,10 +210,30 @@ hipError_t vip_launch(const Geom &g, const T *const num[3], const T *den, const 
 }
 
 template <typename T>
+hipError_t sw_pre2d_launch(const Geom &g, const T *h, const T *const q[3], const T *hp,
+                           const T *const qp[3], double eps, const double k[3], double grav,
+                           const double dx[3], double dt, T *const c[3], T *hc, T *const qs[2],
+                           hipStream_t s)
+{
+    if (g.nd != 2) return hipErrorInvalidValue;
+    k_sw_pre2d<T><<<grid2d(g), SB, 0, s>>>((int)g.n[0], (int)g.n[1], g.bc[0], g.bc[1], h, q[0],
+                                           q[1], hp, qp[0], qp[1], (T)eps, (T)k[0], (T)k[1],
+                                           (T)(-grav), (T)(2.0 * dx[0]), (T)(2.0 * dx[1]),
+                                           (T)(0.5 * dt), c[0], c[1], hc, qs[0], qs[1]);
+    return hipGetLastError();
+}
+
+template <typename T>
 hipError_t sw_force_launch(const Geom &g, const T *h, T *h_prev, T *const q[3],
                            T *const q_prev[3], double grav, const double dx[3], double dt,
                            int save, hipStream_t s)
 {
+    if (g.nd == 2 && !save) {
+        k_sw_force2d<T><<<grid2d(g), SB, 0, s>>>((int)g.n[0], (int)g.n[1], g.bc[0], g.bc[1], h,
+                                                 q[0], q[1], (T)(-grav), (T)(2.0 * dx[0]),
+                                                 (T)(2.0 * dx[1]), (T)(0.5 * dt));
+        return hipGetLastError();
+    }
     const int64_t M = g.n[0] * g.n[1] * g.n[2];
     k_sw_force<T><<<blocks_for(M), SB, 0, s>>>(g, h, h_prev, q[0], q[1], q[2], q_prev[0],
                                                q_prev[1], q_prev[2], (T)(-grav),
@@ -172,9 +259,17 @@ template hipError_t vip_launch<float>(const Geom &, const float *const[3], const
 template hipError_t vip_launch<double>(const Geom &, const double *const[3], const double *,
                                        const double *const[3], const double *, double,
                                        const double[3], double *const[3], hipStream_t);
+template hipError_t sw_pre2d_launch<float>(const Geom &, const float *, const float *const[3],
+                                         const float *, const float *const[3], double,
+                                         const double[3], double, const double[3], double,
+                                         float *const[3], float *, float *const[2], hipStream_t);
 template hipError_t sw_force_launch<float>(const Geom &, const float *, float *, float *const[3],
                                            float *const[3], double, const double[3], double,
                                            int, hipStream_t);
+template hipError_t sw_pre2d_launch<double>(const Geom &, const double *, const double *const[3],
+                                         const double *, const double *const[3], double,
+                                         const double[3], double, const double[3], double,
+                                         double *const[3], double *, double *const[2], hipStream_t);
 template hipError_t sw_force_launch<double>(const Geom &, const double *, double *,
                                             double *const[3], double *const[3], double,
                                             const double[3], double, int, hipStream_t);
