@@ -248,14 +248,19 @@ __global__ void k_donor_adj_walls(Geom g, const T *__restrict__ x, const T *cd, 
 // wall and the right cell of its low wall, and at an open edge also the
 // mapped outside neighbour of the edge wall.  The row is wave-uniform (one
 // block per row segment), so no index division per thread.
-// mode bit 0: write xb (instead of adding to it), plus xadd when given;
-// bit 1: write the wall adjoints (the periodic wall n of a dimension is
-// never written).  z0..z2 (cell fields, NULL when unused, never read here)
+// It writes xb, plus xadd with XADD, and writes (AC) or adds to the wall
+// adjoints (the periodic wall n of a dimension is never written).  z0..z2 (cell fields, NULL when unused, never read here)
 // are set to zero at the thread's cell, for the scatter-add kernels that
 // follow (in place of separate clearing launches).
-template <typename T>
+// A thread makes DR rows of its column: the rows share their reads of yb, c0
+// and x, and all reads of the DR cells are in flight together.  Bound by
+// memory (64 to 72 bytes a cell in FP64), but with one cell per thread the
+// latency of its reads was two thirds of a wave's time.
+constexpr int DR = 4;
+
+template <typename T, bool XADD, bool AC>
 __global__ void __launch_bounds__(B)
-    k_donor_adj2d(int n0, int n1, int bc0, int bc1, int bpr, int flux_is_vel, int mode,
+    k_donor_adj2d(int n0, int n1, int bc0, int bc1, int bpr, int flux_is_vel,
                   const T *__restrict__ x, const T *__restrict__ c0, const T *__restrict__ c1,
                   const T *__restrict__ yb, const T *__restrict__ xadd, T *__restrict__ xb,
                   T *__restrict__ cb0, T *__restrict__ cb1, T *__restrict__ z0,
@@ -270,59 +275,80 @@ __global__ void __launch_bounds__(B)
         const int x8 = blockIdx.x & 7, per = nblk >> 3, rem = nblk & 7;
         b = x8 * per + (x8 < rem ? x8 : rem) + (blockIdx.x >> 3);
     }
-    const int i = b / bpr;
-    const int j = (b - i * bpr) * B + threadIdx.x;
+    const int i0 = b / bpr * DR;
+    const int j = (b % bpr) * B + threadIdx.x;
     if (j >= n1) return;
-    {
-        const int64_t k = (int64_t)i * n1 + j;
+    const bool o0 = bc0 == BC_OPEN, o1 = bc1 == BC_OPEN;
+    const bool lft = o1 && j == 0, rgt = o1 && j == n1 - 1;
+    const int jm = wrap_cell(j - 1, n1, bc1), jp = wrap_cell(j + 1, n1, bc1);
+    const int jw = wrap_wall(j + 1, n1, bc1);
+    // rows i0-1 .. i0+DR (through the boundary map; a row past the last one
+    // of the grid is read in the place of the last and not used)
+    T y[DR + 2], yl[DR], yr[DR], u0[DR + 1], ul[DR], uh[DR], xc[DR + 1], xl[DR];
+    T add[DR], old0[DR], old1[DR];
+#pragma unroll
+    for (int r = 0; r < DR + 2; r++)
+        y[r] = yb[(int64_t)wrap_cell(min(i0 + r - 1, n0), n0, bc0) * n1 + j];
+#pragma unroll
+    for (int r = 0; r < DR; r++) {
+        const int64_t k = (int64_t)min(i0 + r, n0 - 1) * n1;
+        yl[r] = yb[k + jm];
+        yr[r] = yb[k + jp];
+        if (XADD) add[r] = xadd[k + j];
+        if (!AC) {
+            old0[r] = cb0[k + j];
+            old1[r] = cb1[k + min(i0 + r, n0 - 1) + j];
+        }
+    }
+    if (!flux_is_vel) {
+#pragma unroll
+        for (int r = 0; r < DR + 1; r++) {
+            u0[r] = c0[(int64_t)wrap_wall(min(i0 + r, n0), n0, bc0) * n1 + j];
+            xc[r] = x[(int64_t)wrap_cell(min(i0 + r - 1, n0 - 1), n0, bc0) * n1 + j];
+        }
+#pragma unroll
+        for (int r = 0; r < DR; r++) {
+            const int i = min(i0 + r, n0 - 1);
+            ul[r] = c1[(int64_t)i * (n1 + 1) + j];
+            uh[r] = c1[(int64_t)i * (n1 + 1) + jw];
+            xl[r] = x[(int64_t)i * n1 + jm];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < DR; r++) {
+        const int i = i0 + r;
+        if (i >= n0) return;
+        const bool top = o0 && i == 0, bot = o0 && i == n0 - 1;
+        const int64_t k = (int64_t)i * n1 + j, k1 = k + i;
+        const int64_t w0hi = (int64_t)n0 * n1 + j, w1hi = k1 - j + n1;   // edge walls n0, n1
         if (z0) z0[k] = T(0);
         if (z1) z1[k] = T(0);
         if (z2) z2[k] = T(0);
+        const T yc = y[r + 1];
+        const T yim = top ? T(0) : y[r], yip = bot ? T(0) : y[r + 2];
+        const T yjm = lft ? T(0) : yl[r], yjp = rgt ? T(0) : yr[r];
+        const T F0lo = yc - yim, F0hi = yip - yc, F1lo = yc - yjm, F1hi = yjp - yc;
+        T acc = yc, f0 = F0lo, f1 = F1lo, f0h = F0hi, f1h = F1hi;
+        if (!flux_is_vel) {
+            const T u0lo = u0[r], u0hi = u0[r + 1], u1lo = ul[r], u1hi = uh[r];
+            acc = yc + (pos(u0hi) * F0hi + neg(u0lo) * F0lo) + (pos(u1hi) * F1hi + neg(u1lo) * F1lo);
+            if (top) acc += pos(u0lo) * F0lo;
+            if (bot) acc += neg(u0hi) * F0hi;
+            if (lft) acc += pos(u1lo) * F1lo;
+            if (rgt) acc += neg(u1hi) * F1hi;
+            const T xi = xc[r], xo = xc[r + 1], xj = xl[r];
+            f0 = ((u0lo > T(0) ? xi : T(0)) + (u0lo < T(0) ? xo : T(0))) * F0lo;
+            f1 = ((u1lo > T(0) ? xj : T(0)) + (u1lo < T(0) ? xo : T(0))) * F1lo;
+            f0h = ((u0hi > T(0) ? xo : T(0)) + (u0hi < T(0) ? xo : T(0))) * F0hi;
+            f1h = ((u1hi > T(0) ? xo : T(0)) + (u1hi < T(0) ? xo : T(0))) * F1hi;
+        }
+        if (XADD) acc += add[r];
+        xb[k] = acc;
+        cb0[k] = AC ? f0 : old0[r] + f0;
+        cb1[k1] = AC ? f1 : old1[r] + f1;
+        if (bot) cb0[w0hi] = AC ? f0h : cb0[w0hi] + f0h;
+        if (rgt) cb1[w1hi] = AC ? f1h : cb1[w1hi] + f1h;
     }
-    const bool o0 = bc0 == BC_OPEN, o1 = bc1 == BC_OPEN;
-    const bool top = o0 && i == 0, bot = o0 && i == n0 - 1;
-    const bool lft = o1 && j == 0, rgt = o1 && j == n1 - 1;
-    const int64_t r = (int64_t)i * n1;
-    const int64_t rm = (int64_t)wrap_cell(i - 1, n0, bc0) * n1;
-    const int64_t rp = (int64_t)wrap_cell(i + 1, n0, bc0) * n1;
-    const int jm = wrap_cell(j - 1, n1, bc1), jp = wrap_cell(j + 1, n1, bc1);
-    const T y = yb[r + j];
-    const T yim = top ? T(0) : yb[rm + j], yip = bot ? T(0) : yb[rp + j];
-    const T yjm = lft ? T(0) : yb[r + jm], yjp = rgt ? T(0) : yb[r + jp];
-    const T F0lo = y - yim, F0hi = yip - y, F1lo = y - yjm, F1hi = yjp - y;
-    const int64_t w0lo = r + j, w0hi = (int64_t)n0 * n1 + j;          // edge wall n0
-    const int64_t r1 = (int64_t)i * (n1 + 1);
-    const int64_t w1lo = r1 + j, w1hi = r1 + n1;                       // edge wall n1
-    const bool ax = mode & 1, ac = mode & 2;
-    auto put = [](bool assign, T *a, int64_t k, T v) {
-        if (assign)
-            a[k] = v;
-        else
-            a[k] += v;
-    };
-    if (flux_is_vel) {
-        put(ax, xb, r + j, xadd ? y + xadd[r + j] : y);
-        put(ac, cb0, w0lo, F0lo);
-        put(ac, cb1, w1lo, F1lo);
-        if (bot) put(ac, cb0, w0hi, F0hi);
-        if (rgt) put(ac, cb1, w1hi, F1hi);
-        return;
-    }
-    const T u0lo = c0[w0lo], u0hi = c0[(int64_t)wrap_wall(i + 1, n0, bc0) * n1 + j];
-    const T u1lo = c1[w1lo], u1hi = c1[r1 + wrap_wall(j + 1, n1, bc1)];
-    T acc = y + (pos(u0hi) * F0hi + neg(u0lo) * F0lo) + (pos(u1hi) * F1hi + neg(u1lo) * F1lo);
-    if (top) acc += pos(u0lo) * F0lo;
-    if (bot) acc += neg(u0hi) * F0hi;
-    if (lft) acc += pos(u1lo) * F1lo;
-    if (rgt) acc += neg(u1hi) * F1hi;
-    if (xadd) acc += xadd[r + j];
-    put(ax, xb, r + j, acc);
-    const T xc = x[r + j];
-    const T xi = x[rm + j], xj = x[r + jm];
-    put(ac, cb0, w0lo, ((u0lo > T(0) ? xi : T(0)) + (u0lo < T(0) ? xc : T(0))) * F0lo);
-    put(ac, cb1, w1lo, ((u1lo > T(0) ? xj : T(0)) + (u1lo < T(0) ? xc : T(0))) * F1lo);
-    if (bot) put(ac, cb0, w0hi, ((u0hi > T(0) ? xc : T(0)) + (u0hi < T(0) ? xc : T(0))) * F0hi);
-    if (rgt) put(ac, cb1, w1hi, ((u1hi > T(0) ? xc : T(0)) + (u1hi < T(0) ? xc : T(0))) * F1hi);
 }
 
 // Deterministic transpose of the pseudo-velocity (1-D, 3-D, and 2-D with
@@ -675,6 +701,11 @@ constexpr int NQ0 = Q0R * Q0C, NQ1 = Q1R * Q1C;
 // beside them on the +o / -o side (the B term), to the dimension-o walls of
 // its cross-advector mean (a quarter each), and to its own advector
 enum { KR, KL, KP, KM, KQ, KU, NK };
+// halo walls of a tile, dimension 0: the row below it, then the columns at
+// its sides; dimension 1: the rows above and below, then the column past it
+constexpr int H0 = NQ0 - GT, H1 = NQ1 - GT;
+constexpr int H1_FROM = (H0 + 63) / 64 * 64;      // the first thread of dimension 1's (a whole wave)
+static_assert(H1_FROM + H1 <= GT, "the halo walls of both dimensions take one round");
 
 template <typename T, int WD, int BC0, int BC1>
 __device__ __forceinline__ void pseudo_coef2(const Map2<BC0, BC1> &g, unsigned opts,
@@ -717,8 +748,11 @@ k_pseudo_adj2g(Geom gg, unsigned opts, const T *__restrict__ x, const T *c0, con
                T *cb1)
 {
     const Map2<BC0, BC1> g{(int)gg.n[0], (int)gg.n[1]};
-    __shared__ T K0[NK][NQ0];
-    __shared__ T K1[NK][NQ1];
+    // (a wall's own adjoint is read by another thread only where a far edge
+    // wall is owned by the cell below it)
+    constexpr int NK0 = BC0 == BC_OPEN ? NK : KU, NK1 = BC1 == BC_OPEN ? NK : KU;
+    __shared__ T K0[NK0][NQ0];
+    __shared__ T K1[NK1][NQ1];
     const int n0 = g.n0, n1 = g.n1;
     const int tiles_c = (n1 + GC - 1) / GC;
     const int i0 = (int)(blockIdx.x / tiles_c) * GR, j0 = (int)(blockIdx.x % tiles_c) * GC;
@@ -728,9 +762,8 @@ k_pseudo_adj2g(Geom gg, unsigned opts, const T *__restrict__ x, const T *c0, con
     const T *c[2] = {c0, c1};
     // the stencil loads do not wait for the test of vb (a zero vb zeroes
     // the coefficients afterwards)
-    for (int e = threadIdx.x; e < NQ0; e += GT) {
+    auto wall0 = [&](int i, int j) -> T {
         T k[NK] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-        const int i = i0 + e / Q0C, j = j0 - 1 + e % Q0C;
         bool ok = i <= ilim && j <= jlim;
         if (BC1 == BC_OPEN) ok = ok && j >= 0 && j < n1;
         if (ok) {
@@ -740,12 +773,13 @@ k_pseudo_adj2g(Geom gg, unsigned opts, const T *__restrict__ x, const T *c0, con
 #pragma unroll
                 for (int r = 0; r < NK; r++) k[r] = T(0);
         }
+        const int e = (i - i0) * Q0C + (j - (j0 - 1));
 #pragma unroll
-        for (int r = 0; r < NK; r++) K0[r][e] = k[r];
-    }
-    for (int f = threadIdx.x; f < NQ1; f += GT) {
+        for (int r = 0; r < NK0; r++) K0[r][e] = k[r];
+        return k[KU];
+    };
+    auto wall1 = [&](int i, int j) -> T {
         T k[NK] = {T(0), T(0), T(0), T(0), T(0), T(0)};
-        const int i = i0 - 1 + f / Q1C, j = j0 + f % Q1C;
         bool ok = i <= ilim && j <= jlim;
         if (BC0 == BC_OPEN) ok = ok && i >= 0 && i < n0;
         if (ok) {
@@ -755,11 +789,23 @@ k_pseudo_adj2g(Geom gg, unsigned opts, const T *__restrict__ x, const T *c0, con
 #pragma unroll
                 for (int r = 0; r < NK; r++) k[r] = T(0);
         }
+        const int f = (i - (i0 - 1)) * Q1C + (j - j0);
 #pragma unroll
-        for (int r = 0; r < NK; r++) K1[r][f] = k[r];
+        for (int r = 0; r < NK1; r++) K1[r][f] = k[r];
+        return k[KU];
+    };
+    const int tid = (int)threadIdx.x;
+    const int qi = i0 + tid / GC, qj = j0 + tid % GC;
+    const T own0 = wall0(qi, qj), own1 = wall1(qi, qj);
+    if (tid < H0) {
+        if (tid < Q0C) (void)wall0(i0 + GR, j0 - 1 + tid);
+        else (void)wall0(i0 + (tid - Q0C) / 2, (tid - Q0C) % 2 ? j0 + GC : j0 - 1);
+    } else if (tid >= H1_FROM && tid < H1_FROM + H1) {
+        const int f = tid - H1_FROM;
+        if (f < 2 * Q1C) (void)wall1(f < Q1C ? i0 - 1 : i0 + GR, j0 + (f < Q1C ? f : f - Q1C));
+        else (void)wall1(i0 + f - 2 * Q1C, j0 + GC);
     }
     __syncthreads();
-    const int qi = i0 + (int)threadIdx.x / GC, qj = j0 + (int)threadIdx.x % GC;
     if (qi >= n0 || qj >= n1) return;
     // coefficient kind r of the wall at unmapped (i, j); zero outside the
     // box.  The cell's own position and its neighbours are always inside
@@ -809,12 +855,12 @@ k_pseudo_adj2g(Geom gg, unsigned opts, const T *__restrict__ x, const T *c0, con
                k1(CK, KQ, Y0 - 1, Z1);
     };
     {
-        T v = k0(Un{}, KU, qi, qj);
+        T v = own0;
         v += cross0(Un{}, qi, qj);
         for (int t = 1; t < nc; t++) v += cross0(Ck{}, qi, pc[t]);
         cb0[(int64_t)qi * n1 + qj] += v;
     }
-    if (BC0 == BC_OPEN && qi == n0 - 1) {
+    if constexpr (BC0 == BC_OPEN) if (qi == n0 - 1) {
         T v = k0(Ck{}, KU, n0, qj);
         for (int t = 0; t < nc; t++) v += cross0(Ck{}, n0, pc[t]);
         cb0[(int64_t)n0 * n1 + qj] += v;
@@ -824,12 +870,12 @@ k_pseudo_adj2g(Geom gg, unsigned opts, const T *__restrict__ x, const T *c0, con
                k0(CK, KQ, Z0, Y1 - 1);
     };
     {
-        T v = k1(Un{}, KU, qi, qj);
+        T v = own1;
         v += cross1(Un{}, qi, qj);
         for (int s = 1; s < nr; s++) v += cross1(Ck{}, pr[s], qj);
         cb1[(int64_t)qi * (n1 + 1) + qj] += v;
     }
-    if (BC1 == BC_OPEN && qj == n1 - 1) {
+    if constexpr (BC1 == BC_OPEN) if (qj == n1 - 1) {
         T v = k1(Ck{}, KU, qi, n1);
         for (int s = 0; s < nr; s++) v += cross1(Ck{}, pr[s], n1);
         cb1[(int64_t)qi * (n1 + 1) + n1] += v;
@@ -1394,21 +1440,25 @@ bool fast_donor_adj(const Geom &g, const void *G)
 }
 
 // transpose of a donor-cell pass: xb += (dy/dx)^T yb, cb_d += (dy/dc_d)^T yb;
-// with the 2-D kernel, mode bit 0 writes xb (= ... + xadd) and bit 1 writes
-// the wall adjoints instead of adding (other paths: mode must be 0)
+// the 2-D kernel (fast_donor_adj) writes xb (= ... + xadd), and with
+// write_walls the wall adjoints, instead of adding
 // (2-D kernel only: zero[] cell fields are set to zero, see k_donor_adj2d)
 template <typename T>
 void donor_adj(const Geom &g, const T *x, const T *const c[3], const T *G, int flux_is_vel,
-               const T *yb, T *xb, T *const cb[3], hipStream_t s, int mode = 0,
+               const T *yb, T *xb, T *const cb[3], hipStream_t s, bool write_walls = false,
                const T *xadd = nullptr, T *const *zero = nullptr)
 {
     const int64_t N = g.n[0] * g.n[1] * g.n[2];
     if (fast_donor_adj(g, G)) {
         const int bpr = (int)cdiv(g.n[1], B);
-        k_donor_adj2d<T><<<(unsigned)(bpr * g.n[0]), B, 0, s>>>(
-            (int)g.n[0], (int)g.n[1], g.bc[0], g.bc[1], bpr, flux_is_vel, mode, x, c[0], c[1],
-            yb, xadd, xb, cb[0], cb[1], zero ? zero[0] : nullptr, zero ? zero[1] : nullptr,
-            zero ? zero[2] : nullptr);
+        auto go = [&](auto kern) {
+            kern<<<(unsigned)(bpr * cdiv(g.n[0], DR)), B, 0, s>>>(
+                (int)g.n[0], (int)g.n[1], g.bc[0], g.bc[1], bpr, flux_is_vel, x, c[0], c[1], yb,
+                xadd, xb, cb[0], cb[1], zero ? zero[0] : nullptr, zero ? zero[1] : nullptr,
+                zero ? zero[2] : nullptr);
+        };
+        if (xadd) go(write_walls ? k_donor_adj2d<T, true, true> : k_donor_adj2d<T, true, false>);
+        else go(write_walls ? k_donor_adj2d<T, false, true> : k_donor_adj2d<T, false, false>);
         return;
     }
     with_nd(g.nd, [&](auto ND) {
@@ -1759,9 +1809,8 @@ hipError_t reverse_step(const AdjArgs<T> &a, AdjWs<T> &w, const T *psi_n, hipStr
         // corrective donor-cell pass
         {
             const T *Wc[3] = {w.W[it - 1][0], w.W[it - 1][1], w.W[it - 1][2]};
-            const int mode = fast ? (1 | (it == n ? 2 : 0)) : 0;
             T *const zero[3] = {it == n ? w.pnb : nullptr, nullptr, nullptr};
-            donor_adj<T>(g, x, Wc, a.G, iga ? 1 : 0, w.yb, w.xb, w.Ab, s, mode, nullptr,
+            donor_adj<T>(g, x, Wc, a.G, iga ? 1 : 0, w.yb, w.xb, w.Ab, s, fast && it == n, nullptr,
                          fast ? zero : nullptr);
         }
         // limiter
@@ -1801,7 +1850,8 @@ hipError_t reverse_step(const AdjArgs<T> &a, AdjWs<T> &w, const T *psi_n, hipStr
     if (fast) {
         // (pnb was zeroed by the first reversed pass; with no corrective
         // pass there is nothing to add)
-        donor_adj<T>(g, psi_n, a.c, a.G, 0, w.yb, w.xb, w.Cb, s, 1, n >= 2 ? w.pnb : nullptr);
+        donor_adj<T>(g, psi_n, a.c, a.G, 0, w.yb, w.xb, w.Cb, s, false,
+                     n >= 2 ? w.pnb : nullptr);
     } else {
         e = fill<T>(w.xb, N, s);
         donor_adj<T>(g, psi_n, a.c, a.G, 0, w.yb, w.xb, w.Cb, s);
