@@ -202,19 +202,22 @@ template <bool TOT> constexpr int unroll() { return TOT ? 8 : 4; }
 // first chunks start at row 0 with the rows above filled with row 0.
 // HG: G is an array (loaded with the cell rows, row a at age CO); otherwise
 // G = 1.
-// VAR: what a launch may be asked for beside y (Variant): the plain and
-// divergent-flow ones write y only and the recording one the walls and
-// records, none with Kahan's summation; the general one decides it all at
-// run time.  Every run-time choice is a branch in every row, which splits
+// VAR: what a launch is asked for beside y (Variant): the plain and
+// divergent-flow ones write y only, the walls one the limited velocities for
+// a following pass too, the recording one those and every record there is
+// (and y if asked), none with Kahan's summation; the general one decides it
+// all at run time.  Every run-time choice is a branch in every row, which splits
 // the row for the instruction scheduler and adds scalar work that a wave
 // issues in order: with the choices, the 64-bit row offsets formed by
 // multiplications and (FP32) a branch per quotient, a row of the FP64 iga +
 // limiter instance took 212 scalar beside 326 vector instructions.
-enum Variant { V_PLAIN = 0, V_DFL = 1, V_REC = 2, V_ANY = 3 };
+enum Variant { V_PLAIN = 0, V_DFL = 1, V_WALLS = 2, V_REC = 3, V_ANY = 4 };
 
 template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT, int VAR>
 struct March {
-    static constexpr bool OUT = VAR >= V_REC;      // w0, w1 and the records
+    static constexpr bool OUT = VAR >= V_WALLS;    // w0, w1
+    static constexpr bool REC = VAR >= V_REC;      // the records
+    static constexpr bool ASK = VAR == V_ANY;      // whether each is given is asked for
     // what y held before may be kept (the shallow-water fields' option sets:
     // the previous time level, saved here instead of by a copy of its own)
     static constexpr bool SAVE = DONOR && FCT && !HG && !TOT &&
@@ -330,7 +333,7 @@ struct March {
             x_a = open0 && a >= n0 ? AT(xq, XQ, 1) : x_a;   // rows past the end
             pn_a = pc;
             // the donor result of the chunk's own rows and columns
-            if (OUT && xd && a >= i0 && a < i1 && out_lane) (xd + ro)[ocol] = x_a;
+            if (REC && (!ASK || xd) && a >= i0 && a < i1 && out_lane) (xd + ro)[ocol] = x_a;
         } else {
             x_a = fx[S];
             pn_a = fp[S];
@@ -577,22 +580,22 @@ struct March {
 
         // limited velocities for a following pass (and, when asked, the raw
         // velocities and the coefficients): wall rl and row rl
-        if (OUT && w0) {
+        if (OUT && (!ASK || w0)) {
             const int w = rl;
             if (w >= i0 && (w < i1 || (w == n0 && i1 == n0 && open0))) {
                 const int64_t k0 = ro - (int64_t)(1 + SH) * n1;
                 const int64_t k1 = ro1 - (int64_t)(1 + SH) * (n1 + 1);
                 if (out_lane) {
                     (w0 + k0)[ocol] = lim0;
-                    if (v0r) (v0r + k0)[ocol] = AT(v0q, 2, 1);
-                    if (FCT && bur && w < i1) {
+                    if (REC && (ASK ? v0r != nullptr : FCT)) (v0r + k0)[ocol] = AT(v0q, 2, 1);
+                    if (REC && FCT && (!ASK || bur) && w < i1) {
                         (bur + k0)[ocol] = AT(buq, 2, 0);
                         (bdr + k0)[ocol] = AT(bdq, 2, 0);
                     }
                 }
                 if (w < i1 && w1_lane) {
                     (w1 + k1)[ocol] = lim1;
-                    if (v1r) (v1r + k1)[ocol] = v1l;
+                    if (REC && (ASK ? v1r != nullptr : FCT)) (v1r + k1)[ocol] = v1l;
                 }
             }
         }
@@ -623,7 +626,7 @@ struct March {
                 if (r >= i0 && r < i1 && out_lane) (save + ro - (int64_t)(2 + SH) * n1)[ocol] = was;
             }
         }
-        if ((!OUT || y) && r >= i0 && r < i1 && out_lane) (y + ro - (int64_t)(2 + SH) * n1)[ocol] = res;
+        if ((!REC || y) && r >= i0 && r < i1 && out_lane) (y + ro - (int64_t)(2 + SH) * n1)[ocol] = res;
         ro += n1;
         ro1 += n1 + 1;
     }
@@ -802,13 +805,18 @@ hipError_t launch(const PassArgs<T> &p)
 
 // The instance of a launch.  The variants without run-time choices exist for
 // what steps and recordings ask for: y alone (every option), y with the
-// divergent-flow term under iga and the limiter (shallow water), and the
-// walls and records without iga or abs; everything else is V_ANY.
+// divergent-flow term under iga and the limiter (shallow water), y and the
+// walls, or the walls and records, without iga or abs; everything else is
+// V_ANY.
 template <typename T, bool DONOR> hipError_t pass2d_go(const PassArgs<T> &p)
 {
     const bool fct = p.opts & OPT_FCT, iga = p.opts & OPT_IGA, absf = p.opts & OPT_ABS;
     const bool tot = p.opts & OPT_TOT, dfl = p.opts & OPT_DFL, kahan = p.opts & OPT_KAHAN;
-    const bool out = p.w0 || p.rec.xd || p.rec.v0 || p.rec.bu || !p.fl.y[0];
+    const bool out = p.w0 || p.w1 || p.rec.xd || p.rec.v0 || p.rec.bu || !p.fl.y[0];
+    const PassRecord<T> &rec = p.rec;
+    const bool recs = rec.xd || rec.v0 || rec.v1 || rec.bu || rec.bd;
+    const bool all_recs = (!DONOR || rec.xd) && (fct ? rec.v0 && rec.v1 && rec.bu && rec.bd
+                                                     : !rec.v0 && !rec.v1);
     auto by_v = [&](auto F, auto I, auto A, auto H, auto O) {
         constexpr bool f = decltype(F)::value, i = decltype(I)::value, a = decltype(A)::value;
         constexpr bool h = decltype(H)::value, o = decltype(O)::value;
@@ -816,7 +824,10 @@ template <typename T, bool DONOR> hipError_t pass2d_go(const PassArgs<T> &p)
         if constexpr (f && i && !h && !o)
             if (!kahan && !out) return launch<T, f, i, a, DONOR, h, o, V_DFL>(p);
         if constexpr (!i && !a)
-            if (!kahan && !dfl) return launch<T, f, i, a, DONOR, h, o, V_REC>(p);
+            if (!kahan && !dfl && p.w0 && p.w1) {
+                if (!recs && p.fl.y[0]) return launch<T, f, i, a, DONOR, h, o, V_WALLS>(p);
+                if (all_recs) return launch<T, f, i, a, DONOR, h, o, V_REC>(p);
+            }
         return launch<T, f, i, a, DONOR, h, o, V_ANY>(p);
     };
     using TT = std::true_type;
