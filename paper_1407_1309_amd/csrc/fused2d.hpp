@@ -624,8 +624,11 @@ hipError_t launch(const Fused2DShape &sh, const T *psi_n, T *psi_out, const T *c
             // long as the partials' buffer allows for
             static const Slots slots = slots_of((const void *)kern, WAVE);
             constexpr int W = C::NP == 0 ? 0 : 4 * C::NP - 1;
-            th = march_rows(sh.n0, strips, slots, 2 * C::LAG + 1 - W, C::UT,
-                            decltype(DG)::value ? 16 : 4, 0.75 * W);
+            static thread_local ChunkMemo memo;
+            th = memo(sh.n0, strips, [&] {
+                return march_rows(sh.n0, strips, slots, 2 * C::LAG + 1 - W, C::UT,
+                                  decltype(DG)::value ? 16 : 4, 0.75 * W);
+            });
         }
         if (th > sh.n0) th = sh.n0;
         const int64_t blocks = strips * cdiv(sh.n0, th);

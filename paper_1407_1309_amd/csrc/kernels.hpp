@@ -58,6 +58,23 @@ inline int64_t march_rows(int64_t n0, int64_t strips, const Slots &sl, int extra
     return best < n0 ? best : n0;
 }
 
+// The last choice of a chunk rule, kept by each thread for each kernel (the
+// rules depend on their arguments alone): pricing the candidates takes about
+// a microsecond of host time, which a loop of small launches would pay for
+// every step.
+struct ChunkMemo {
+    int64_t n0 = -1, across = -1, rows = 0;
+    template <typename F> int64_t operator()(int64_t n, int64_t strips, F rule)
+    {
+        if (n != n0 || strips != across) {
+            rows = rule();
+            n0 = n;
+            across = strips;
+        }
+        return rows;
+    }
+};
+
 // Arguments of one step through the staged (one launch per stage) path.
 template <typename T> struct StagedArgs {
     Geom g;

@@ -308,6 +308,32 @@ struct March {
         return below ? lo : (above ? hi : v);
     }
 
+    // The rows above an open domain are copies of row 0: before the march of a
+    // chunk that starts there, every ring slot takes the donor result of row
+    // 0 (psi^n rows -1 and 0 are in the rings at phase 0, row 1 is fetched).
+    __device__ __forceinline__ void fill_above()
+    {
+        constexpr int P = 0;
+        const T pc = AT(pq, 4, 1), f0lo = upwind_fp(AT(c0q, 4, 1), AT(pq, 4, 2), pc);
+        const T f0hi = upwind_fp(f0[0], pc, fx[0]);
+        const T f1lo = upwind_fp(AT(c1q, 4, 1), from_left(pc), pc);
+        const T f1hi = from_right(f1lo);
+        T g = T(1);
+        if constexpr (HG) g = AT(gq, GQ, 1);
+        const T x0 = edge_cols(donor_update_g<HG>(with_kahan(), pc, f0hi - f0lo, f1hi - f1lo, g));
+        const T l = from_left(x0), r = from_right(x0);
+#pragma unroll
+        for (int k = 0; k < XQ; k++) xq.v[k] = x0;
+#pragma unroll
+        for (int k = 0; k < XR; k++) xr.v[k] = r;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            xl.v[k] = l;
+            mxq.v[k] = fmax(pc, x0);
+            mnq.v[k] = fmin(pc, x0);
+        }
+    }
+
     // One row.  STAGE: 2, all of it; on the first rows of a chunk, above
     // what any output row reads, 0: the pass input alone, 1: and the raw
     // velocities.
@@ -344,24 +370,6 @@ struct March {
         AT(xq, XQ, 0) = x_a;
         AT(xl, 4, 0) = from_left(x_a);
         AT(xr, XR, 0) = from_right(x_a);
-        if (DONOR && P == 0 && prefill) {   // (a chunk's first row has phase 0)
-            // first row of an open domain: the rows above are copies of it
-            prefill = false;
-#pragma unroll
-            for (int k = 1; k <= 3 + SH; k++) AT(xq, XQ, k) = x_a;
-#pragma unroll
-            for (int k = 1; k <= 2 + SH; k++) AT(xl, 4, k) = AT(xl, 4, 0);
-#pragma unroll
-            for (int k = 1; k <= 1 + SH; k++) AT(xr, XR, k) = AT(xr, XR, 0);
-            if (FCT) {
-#pragma unroll
-                for (int k = 1; k <= 2 + SH; k++) {
-                    AT(mxq, 4, k) = fmax(pn_a, x_a);
-                    AT(mnq, 4, k) = fmin(pn_a, x_a);
-                }
-            }
-        }
-
         if (FCT) {
             AT(mxq, 4, 0) = fmax(pn_a, x_a);
             AT(mnq, 4, 0) = fmin(pn_a, x_a);
@@ -647,17 +655,18 @@ __device__ __forceinline__ void iter_block(M &m, int a)
 // velocities (V0 at wall i0-1, V1 of the limiter's first row), and from
 // then on every stage counts.
 constexpr int LEAD = 4;
+constexpr int LEAD_P = 4;          // their first phase: the row loop follows at phase 0 (of 4 or 8)
 constexpr double LEAD_COST = 2.0;   // in whole rows
 template <typename M> __device__ __forceinline__ void lead_in(M &m, int a)
 {
-    m.template iter<0, 0>(a);
-    m.template iter<1, 0>(a + 1);
+    m.template iter<LEAD_P, 0>(a);
+    m.template iter<LEAD_P + 1, 0>(a + 1);
     if constexpr (M::SH) {
-        m.template iter<2, 0>(a + 2);
-        m.template iter<3, 1>(a + 3);
+        m.template iter<LEAD_P + 2, 0>(a + 2);
+        m.template iter<LEAD_P + 3, 1>(a + 3);
     } else {
-        m.template iter<2, 1>(a + 2);
-        m.template iter<3, 2>(a + 3);
+        m.template iter<LEAD_P + 2, 1>(a + 2);
+        m.template iter<LEAD_P + 3, 2>(a + 3);
     }
 }
 
@@ -759,24 +768,42 @@ __global__ void __launch_bounds__(WAVE)
     m.ro = (int64_t)a_begin * n1;
     m.ro1 = (int64_t)a_begin * (n1 + 1);
     if (DONOR) {
+        // (the ring slots of the first phase: LEAD_P with the lead-in, 0
+        // without, which differ in rings of eight only)
         T vp;
         m.seek(a_begin - 1, a_begin - 1);
-        m.fetch(m.pq.v[slot<4>(0, 2)], vp, m.c1q.v[slot<4>(0, 2)], m.c0q.v[slot<4>(0, 2)],
-                m.gq.v[slot<M::GQ>(0, 2)]);
-        m.fetch(m.pq.v[slot<4>(0, 1)], vp, m.c1q.v[slot<4>(0, 1)], m.c0q.v[slot<4>(0, 1)],
-                m.gq.v[slot<M::GQ>(0, 1)]);
+        auto first = [&](auto PH) {
+            constexpr int ph = decltype(PH)::value;
+            m.fetch(m.pq.v[slot<4>(ph, 2)], vp, m.c1q.v[slot<4>(ph, 2)], m.c0q.v[slot<4>(ph, 2)],
+                    m.gq.v[slot<M::GQ>(ph, 2)]);
+            m.fetch(m.pq.v[slot<4>(ph, 1)], vp, m.c1q.v[slot<4>(ph, 1)], m.c0q.v[slot<4>(ph, 1)],
+                    m.gq.v[slot<M::GQ>(ph, 1)]);
+        };
+        if (M::GQ == 4 || m.prefill) first(std::integral_constant<int, 0>{});
+        else first(std::integral_constant<int, LEAD_P>{});
     } else {
         m.seek(a_begin, a_begin + 1);
     }
 #pragma unroll
     for (int k = 0; k < PF; k++) m.load(k);
+    // A chunk without the lead-in runs a row loop of its own: one loop
+    // entered from both measured 6 % slower (shallow water 1024^2, 67 -> 70 us
+    // a step).  Under TOT, whose rows are three times the code, one loop
+    // serves both: a launch from cold caches is bound by fetching it (256^2
+    // FP64 with G, five steps after other work, 336 -> 200 us).
     constexpr int U = unroll<TOT>();
-    if (m.prefill) {
-        for (int a = a_begin; a <= a_end; a += U) iter_block<U, 0>(m, a);
-        return;
+    int a = a_begin;
+    if (DONOR && m.prefill) {
+        m.fill_above();
+        if constexpr (!TOT) {
+            for (; a <= a_end; a += U) iter_block<U, 0>(m, a);
+            return;
+        }
+    } else {
+        lead_in(m, a);
+        a += LEAD;
     }
-    lead_in(m, a_begin);
-    for (int a = a_begin + LEAD; a <= a_end; a += U) iter_block<U, LEAD>(m, a);
+    for (; a <= a_end; a += U) iter_block<U, 0>(m, a);
 }
 
 template <typename T, bool FCT, bool IGA, bool ABS, bool DONOR, bool HG, bool TOT, int VAR>
@@ -790,7 +817,11 @@ hipError_t launch(const PassArgs<T> &p)
         // a chunk runs th + 5 iterations (one more under TOT), of which the
         // first LEAD do part of the work
         static const Slots slots = slots_of((const void *)kern, WAVE);
-        th = march_rows(n0, strips * p.fields, slots, TOT ? 2 : 1, unroll<TOT>(), 1, LEAD_COST);
+        static thread_local ChunkMemo memo;
+        th = memo(n0, strips * p.fields, [&] {
+            return march_rows(n0, strips * p.fields, slots, TOT ? 2 : 1, unroll<TOT>(), 1,
+                              LEAD_COST);
+        });
     }
     if (th > n0) th = n0;
     const dim3 blocks((unsigned)(strips * cdiv(n0, th)), (unsigned)p.fields);

@@ -33,8 +33,8 @@ LineShape line1d_whole(int64_t n, int n_iters, unsigned opts)
     return sh;
 }
 
-LineShape line1d_tiled(int64_t n, int f64, int n_iters, unsigned opts, int fields, int n_steps,
-                       int *launches)
+static LineShape tiled_shape(int64_t n, int f64, int n_iters, unsigned opts, int fields,
+                             int n_steps, int *launches)
 {
     // cost in microseconds: a launch, a step's chain of dependent operations
     // and its barrier, and the issue of a step's operations for one cell per
@@ -70,6 +70,26 @@ LineShape line1d_tiled(int64_t n, int f64, int n_iters, unsigned opts, int field
         if (best.K && L * LAUNCH > best_cost) break;
     }
     return best;
+}
+
+LineShape line1d_tiled(int64_t n, int f64, int n_iters, unsigned opts, int fields, int n_steps,
+                       int *launches)
+{
+    // the last choice, kept by each thread (see ChunkMemo)
+    struct Memo {
+        int64_t n = -1;
+        int f64, n_iters, fields, n_steps, launches;
+        unsigned opts;
+        LineShape sh;
+    };
+    static thread_local Memo m;
+    if (m.n != n || m.f64 != f64 || m.n_iters != n_iters || m.opts != opts ||
+        m.fields != fields || m.n_steps != n_steps) {
+        m = Memo{n, f64, n_iters, fields, n_steps, 0, opts, LineShape{}};
+        m.sh = tiled_shape(n, f64, n_iters, opts, fields, n_steps, &m.launches);
+    }
+    *launches = m.launches;
+    return m.sh;
 }
 
 template hipError_t line1d_launch<double>(const LineShape &, const LineArgs<double> &, int,

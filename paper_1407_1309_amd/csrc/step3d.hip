@@ -802,7 +802,10 @@ hipError_t step3d_launch(const Geom &geom, unsigned opts, const T *psi_n, T *psi
         int th = tile_planes;
         if (th <= 0) {
             static const Slots slots = slots_of((const void *)kern, NT);
-            th = planes_per_chunk(tiles, g.n0, slots.cus, slots.per_cu);
+            static thread_local ChunkMemo memo;
+            th = (int)memo(g.n0, tiles, [&] {
+                return planes_per_chunk(tiles, g.n0, slots.cus, slots.per_cu);
+            });
         }
         if (th > g.n0) th = g.n0;
         const int64_t blocks = tiles * cdiv(g.n0, th);
