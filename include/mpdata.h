@@ -377,7 +377,8 @@ int mpdata_step_per_grid(mpdata_plan *plan, void *psi_packed,
 /* Timing of the step kernels, for roofline accounting.  mpdata_timing(plan,
  * m) with m > 0 clears earlier records and times the next m step launches
  * made by mpdata_step (the fused 2-D kernel, the 3-D donor + corrective
- * pair, the resident 1-D kernel -- one launch for all steps of a call -- or
+ * pair, the 1-D kernel (one launch for all steps of a call, on longer grids
+ * one for several steps) or
  * the staged kernel sequence): a HIP event on the plan's stream before the
  * first of them and one after the m-th (or, if fewer were made, one
  * recorded by mpdata_timing_read), with no event in between, so time
