@@ -27,14 +27,11 @@ CFLAGS = ["-std=c++17", "-O3", "-fPIC", f"--offload-arch={ARCH}",
 # extra instruction per operand); its row loop is one long basic block per
 # row, which the back end's ILP-first scheduler interleaves better (measured:
 # 2-D FP64 -1.9 %, FP32 -4 %, batched FP32 -5 %; the same bits).
-# The 1-D resident kernel likewise (1-D step -3 %, oscillator -2 %).  The
-# 2-D single pass assumes NaN-free data for the same reason.
+# The 1-D resident kernel likewise (1-D step -3 %, oscillator -2 %).
 _FUSED2D = ["-fno-honor-nans", "-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 _LINE1D = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 FILE_FLAGS = {"fused2d_f32.hip": _FUSED2D, "fused2d_f64.hip": _FUSED2D,
-              "resident1d.hip": _LINE1D, "resident1d_f32.hip": _LINE1D,
-              **{f"pass2d_{t}_{d}.hip": ["-fno-honor-nans"]
-                 for t in ("f64", "f32") for d in ("donor", "pass")}}
+              "resident1d.hip": _LINE1D, "resident1d_f32.hip": _LINE1D}
 
 
 def sources():
