@@ -547,14 +547,10 @@ int run_steps(mpdata_plan *p, T *psi, const T *G, const T *c0, const T *c1, cons
     return p->step_diag ? step_diag_finish<T>(p, psi, G, dparts) : MPDATA_OK;
 }
 
-// mpdata_step with an optional source term ahead of it (see run_steps)
-int checked_steps(mpdata_plan *plan, void *psi, const void *g, const void *c0, const void *c1,
-                  const void *c2, int n_steps, const void *r_pre, double a_pre)
+// the advector and G a step call must be given
+int step_args(const mpdata_plan *plan, const void *g, const void *c0, const void *c1,
+              const void *c2)
 {
-    if (!plan) return fail(MPDATA_EINVAL, "plan is NULL");
-    if (plan->batched) return fail(MPDATA_EINVAL, "batched plan: use mpdata_step_batched");
-    if (!psi) return fail(MPDATA_EINVAL, "psi is NULL");
-    if (n_steps < 0) return fail(MPDATA_EINVAL, "n_steps < 0");
     const void *c[3] = {c0, c1, c2};
     for (int d = 0; d < 3; d++) {
         if (d < plan->desc.n_dims && !c[d]) return fail(MPDATA_EINVAL, "c%d is NULL", d);
@@ -564,6 +560,19 @@ int checked_steps(mpdata_plan *plan, void *psi, const void *g, const void *c0, c
     if ((g != nullptr) != (plan->desc.has_g != 0))
         return fail(MPDATA_EINVAL, plan->desc.has_g ? "plan has_g but g is NULL"
                                                     : "g given but plan was made without has_g");
+    return MPDATA_OK;
+}
+
+// mpdata_step with an optional source term ahead of it (see run_steps)
+int checked_steps(mpdata_plan *plan, void *psi, const void *g, const void *c0, const void *c1,
+                  const void *c2, int n_steps, const void *r_pre, double a_pre)
+{
+    if (!plan) return fail(MPDATA_EINVAL, "plan is NULL");
+    if (plan->batched) return fail(MPDATA_EINVAL, "batched plan: use mpdata_step_batched");
+    if (!psi) return fail(MPDATA_EINVAL, "psi is NULL");
+    if (n_steps < 0) return fail(MPDATA_EINVAL, "n_steps < 0");
+    int rc = step_args(plan, g, c0, c1, c2);
+    if (rc) return rc;
     if (plan->desc.dtype == MPDATA_F64)
         return run_steps<double>(plan, (double *)psi, (const double *)g, (const double *)c0,
                                  (const double *)c1, (const double *)c2, n_steps,
@@ -848,6 +857,8 @@ int mpdata_osc_step(mpdata_plan *plan, void *psi, void *phi, const void *g, cons
     const int64_t N = cells_of(plan->g);
     const bool f64 = plan->desc.dtype == MPDATA_F64;
     if (n_steps == 0) return MPDATA_OK;
+    int rc = step_args(plan, g, c0, c1, c2);
+    if (rc) return rc;
     if (plan->kernel != MPDATA_KERNEL_STAGED &&
         mp::resident1d_supported(plan->desc.n_dims, plan->g.n[0], f64, plan->desc.has_g, 1)) {
         // 1-D pair resident in LDS: every step of the call in one launch
@@ -861,10 +872,8 @@ int mpdata_osc_step(mpdata_plan *plan, void *psi, void *phi, const void *g, cons
         if (tm) timer_end(plan);
         return e == hipSuccess ? MPDATA_OK : hip_fail(e, "resident oscillator launch");
     }
-    // a longer 1-D pair: tiled launches of several steps (what mpdata_step
-    // refuses is left to it below)
-    if (step_path(plan) == PATH_LINE && !plan->cancel && !plan->step_diag && c0 && !c1 && !c2 &&
-        (g != nullptr) == (plan->desc.has_g != 0))
+    // a longer 1-D pair: tiled launches of several steps
+    if (step_path(plan) == PATH_LINE && !plan->cancel && !plan->step_diag)
         return f64 ? line_steps<double>(plan, (double *)psi, (double *)phi, (const double *)c0,
                                         (const double *)g, n_steps, a)
                    : line_steps<float>(plan, (float *)psi, (float *)phi, (const float *)c0,
@@ -875,7 +884,7 @@ int mpdata_osc_step(mpdata_plan *plan, void *psi, void *phi, const void *g, cons
                            : mp::osc_couple_launch<float>((float *)psi, (float *)phi, a, 0, N,
                                                           plan->stream);
         if (e != hipSuccess) return hip_fail(e, "oscillator coupling launch");
-        int rc = mpdata_step(plan, psi, g, c0, c1, c2, 1);
+        rc = mpdata_step(plan, psi, g, c0, c1, c2, 1);
         if (rc) return rc;
         rc = mpdata_step(plan, phi, g, c0, c1, c2, 1);
         if (rc) return rc;
