@@ -619,15 +619,13 @@ hipError_t launch(const Fused2DShape &sh, const T *psi_n, T *psi_out, const T *c
         auto kern = k_fused2d<T, NI, FCT, ABS, KH, decltype(DG)::value>;
         int64_t th = sh.tile_rows;
         if (th <= 0) {
-            // a chunk runs th + 2 LAG + 1 iterations, the warm-up ones
-            // (W) at part of the work; one with diagnostics is at least as
-            // long as the partials' buffer allows for
+            static_assert(C::LAG == 1 + 2 * C::NP && C::UT == (NI <= 3 ? 4 : 8),
+                          "what fused2d_rows prices");
             static const Slots slots = slots_of((const void *)kern, WAVE);
-            constexpr int W = C::NP == 0 ? 0 : 4 * C::NP - 1;
             static thread_local ChunkMemo memo;
             th = memo(sh.n0, strips, [&] {
-                return march_rows(sh.n0, strips, slots, 2 * C::LAG + 1 - W, C::UT,
-                                  decltype(DG)::value ? 16 : 4, 0.75 * W);
+                return fused2d_rows(sh.n0, strips, slots, NI, sizeof(T) == 8,
+                                    decltype(DG)::value);
             });
         }
         if (th > sh.n0) th = sh.n0;

@@ -5,58 +5,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "chunks.hpp"
 #include "common.hpp"
 
 namespace mp {
 
-// What the chip holds of a kernel at once: compute units and workgroups per
-// unit (from the runtime's occupancy query; the figures of a gfx950, 256
-// units and one workgroup, if it fails).  For the rules that choose how much
-// of a grid one workgroup takes; results never depend on it.
-struct Slots {
-    int cus, per_cu;
-};
-// (kernel NULL: the number of units only)
+// (see Slots; kernel NULL: the number of units only)
 Slots slots_of(const void *kernel, int threads, size_t lds = 0);
-
-// Rows per chunk of a 2-D row march (one wave per strip and chunk) when the
-// caller set none.  A chunk of th rows costs its wave extra + th iterations,
-// in whole blocks of `unit` (and `lead` more before them); with w waves on each SIMD an iteration takes
-// 1.5 + w units of time (the part that waits on its own dependencies, and
-// the issue slots the waves share), and waves beyond what the chip holds
-// wait for another round.  Priced for every number of waves per SIMD up to
-// what fits and for some more rounds; the cheapest wins, ties to the longer
-// chunk.  The 1.5 is fitted to sweeps of 4 to 128 rows over 61 x 77 to
-// 3000 x 3000, FP32 and FP64: the choice is 1.6 % slower than the best chunk
-// of each size in the geometric mean (rules of a fixed number of waves and
-// at least 16 or 11 rows: 34 % slower).
-inline int64_t march_rows(int64_t n0, int64_t strips, const Slots &sl, int extra, int unit,
-                          int min_rows, double lead = 0.0)
-{
-    constexpr int SIMDS = 4, MORE = 8;
-    constexpr double WAIT = 1.5;
-    const int64_t per_round = (int64_t)sl.cus * sl.per_cu, simds = (int64_t)sl.cus * SIMDS;
-    const int wps = sl.per_cu >= SIMDS ? sl.per_cu / SIMDS : 1;
-    int64_t best = n0;
-    double best_cost = 0.0;
-    for (int k = 1; k <= wps + MORE; k++) {
-        const int64_t waves = k <= wps ? k * simds : (int64_t)(k - wps + 1) * per_round;
-        int64_t chunks = waves / (strips > 0 ? strips : 1);
-        if (chunks < 1) chunks = 1;
-        int64_t th = cdiv(n0, chunks);
-        if (th < min_rows) th = min_rows;
-        th = cdiv(th + extra, unit) * unit - extra;
-        const int64_t all = strips * cdiv(n0, th), rest = all % per_round;
-        const double cost = ((double)(th + extra) + lead) *
-                            ((double)(all / per_round) * (WAIT + wps) +
-                             (rest ? WAIT + (double)cdiv(rest, simds) : 0.0));
-        if (k == 1 || cost < best_cost || (cost == best_cost && th > best)) {
-            best_cost = cost;
-            best = th;
-        }
-    }
-    return best < n0 ? best : n0;
-}
 
 // The last choice of a chunk rule, kept by each thread for each kernel (the
 // rules depend on their arguments alone): pricing the candidates takes about

@@ -656,7 +656,6 @@ __device__ __forceinline__ void iter_block(M &m, int a)
 // then on every stage counts.
 constexpr int LEAD = 4;
 constexpr int LEAD_P = 4;          // their first phase: the row loop follows at phase 0 (of 4 or 8)
-constexpr double LEAD_COST = 2.0;   // in whole rows
 template <typename M> __device__ __forceinline__ void lead_in(M &m, int a)
 {
     m.template iter<LEAD_P, 0>(a);
@@ -814,13 +813,11 @@ hipError_t launch(const PassArgs<T> &p)
     auto kern = k_pass2d<T, FCT, IGA, ABS, DONOR, HG, TOT, VAR>;
     int64_t th = p.tile_rows;
     if (th <= 0) {
-        // a chunk runs th + 5 iterations (one more under TOT), of which the
-        // first LEAD do part of the work
+        static_assert(LEAD == 4 && unroll<TOT>() == (TOT ? 8 : 4), "what pass2d_rows prices");
         static const Slots slots = slots_of((const void *)kern, WAVE);
         static thread_local ChunkMemo memo;
         th = memo(n0, strips * p.fields, [&] {
-            return march_rows(n0, strips * p.fields, slots, TOT ? 2 : 1, unroll<TOT>(), 1,
-                              LEAD_COST);
+            return pass2d_rows(n0, strips * p.fields, slots, TOT, sizeof(T) == 8);
         });
     }
     if (th > n0) th = n0;
