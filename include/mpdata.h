@@ -138,9 +138,10 @@ int mpdata_set_kernel(mpdata_plan *plan, int kernel);
 int mpdata_set_tile_rows(mpdata_plan *plan, int rows);
 
 /* Autotuner: time the fused step on the caller's inputs for a set of chunk
- * lengths (psi is read, not modified; results go to workspace) and keep the
- * fastest in the plan.  *out_tile_rows receives the choice (0 when the plan
- * runs the staged path, which has nothing to tune).  Waits for completion. */
+ * lengths, the built-in choice among them (psi is read, not modified; results
+ * go to workspace), and keep the fastest in the plan.  *out_tile_rows
+ * receives the choice (0 when the plan runs the staged path, which has
+ * nothing to tune).  Waits for completion. */
 int mpdata_autotune(mpdata_plan *plan, const void *psi, const void *g,
                     const void *c0, const void *c1, const void *c2,
                     int *out_tile_rows);

@@ -138,10 +138,6 @@ struct Layout {
     size_t bytes;
 };
 
-// fused 2-D chunks shorter than this run without the in-kernel diagnostics
-// (the partial buffer is sized for chunks of at least this many rows)
-constexpr int SDIAG_MIN_ROWS = 16;
-
 Layout carve(const mp::Geom &g, int dtype, void *base, int n_iters = 1, unsigned opts = 0)
 {
     Layout L;
@@ -154,7 +150,8 @@ Layout carve(const mp::Geom &g, int dtype, void *base, int n_iters = 1, unsigned
     L.sdiag = (double *)c.take(sizeof(double) * 8);
     if (g.nd == 2)
         L.spart = (double *)c.take(
-            sizeof(double) * 5 * mp::fused2d_max_parts(g.n[0], g.n[1], n_iters, opts, SDIAG_MIN_ROWS));
+            sizeof(double) * 5 * mp::fused2d_max_parts(g.n[0], g.n[1], n_iters, opts,
+                                                      mp::FUSED2D_DIAG_ROWS));
     L.psi_alt = c.take(es * N);
     L.tmp[0] = c.take(es * N);
     L.tmp[1] = c.take(es * N);
@@ -176,6 +173,7 @@ struct mpdata_plan {
     hipStream_t stream;
     int kernel;
     int tile_rows = 0;   // fused kernel rows per wavefront chunk (0 = default)
+    int rows_used = 0;   // rows (planes) of the last fused step's chunks
     Layout L;
     // batched plans
     bool batched = false;
@@ -285,9 +283,10 @@ int one_step(mpdata_plan *p, const T *psi_n, T *psi_out, const T *G, const T *c0
         w.bup = (T *)p->L.bup;
         w.bdn = (T *)p->L.bdn;
         e = mp::fused3d_step<T>(p->g, p->desc.n_iters, p->desc.opts, psi_n, psi_out, c0, c1, c2,
-                                G, p->tile_rows, p->stream, w);
+                                G, p->tile_rows, p->stream, w, &p->rows_used);
     } else if (fused) {
-        mp::Fused2DShape sh{p->g.n[0], p->g.n[1], p->g.bc[0], p->g.bc[1], p->tile_rows};
+        mp::Fused2DShape sh{p->g.n[0], p->g.n[1], p->g.bc[0], p->g.bc[1], p->tile_rows,
+                            &p->rows_used};
         e = mp::fused2d_step<T>(sh, p->desc.n_iters, p->desc.opts, psi_n, psi_out, c0, c1, G,
                                 p->stream, dparts ? p->L.spart : nullptr, dparts);
     } else {
@@ -420,8 +419,7 @@ int step_diag_finish(mpdata_plan *p, const T *psi, const T *G, int dparts)
 // true when the fused 2-D step can write the diagnostics partials itself
 bool step_diag_in_kernel(const mpdata_plan *p, int path)
 {
-    return p->step_diag && path == PATH_FUSED && p->desc.n_dims == 2 &&
-           (p->tile_rows == 0 || p->tile_rows >= SDIAG_MIN_ROWS);
+    return p->step_diag && path == PATH_FUSED && p->desc.n_dims == 2;
 }
 
 // Step loop with a stop flag: every step runs to completion (stream
@@ -730,34 +728,41 @@ int mpdata_autotune(mpdata_plan *plan, const void *psi, const void *g, const voi
     const void *c[3] = {c0, c1, c2};
     for (int d = 0; d < plan->desc.n_dims; d++)
         if (!c[d]) return fail(MPDATA_EINVAL, "c%d is NULL", d);
-    static const int cand[] = {16, 24, 32, 40, 48, 64, 80, 96, 128, 160, 192, 256, 384, 512};
+    static const int cand[] = {4, 8, 12, 16, 24, 32, 40, 48, 64, 80, 96, 128, 160, 192, 256, 384, 512};
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return fail(MPDATA_EHIP, "hipEventCreate");
     if (hipEventCreate(&e1) != hipSuccess) {
         (void)hipEventDestroy(e0);
         return fail(MPDATA_EHIP, "hipEventCreate");
     }
-    int saved = plan->tile_rows, best = 0;
+    const int saved = plan->tile_rows;
+    int best = 0, rc = MPDATA_OK;
     float best_ms = 0.0f;
-    int rc = MPDATA_OK;
+    auto step = [&]() {
+        return plan->desc.dtype == MPDATA_F64
+                   ? one_step<double>(plan, (const double *)psi, (double *)plan->L.psi_alt,
+                                      (const double *)g, (const double *)c0, (const double *)c1,
+                                      (const double *)c2, PATH_FUSED)
+                   : one_step<float>(plan, (const float *)psi, (float *)plan->L.psi_alt,
+                                     (const float *)g, (const float *)c0, (const float *)c1,
+                                     (const float *)c2, PATH_FUSED);
+    };
+    // the built-in choice is a candidate like the others, by its length
+    plan->tile_rows = plan->rows_used = 0;
+    rc = step();
+    const int own = plan->rows_used;
     const int ncand = (int)(sizeof cand / sizeof cand[0]);
     // two sweeps over the candidates; the minimum time of each counts
-    for (int kk = 0; kk < 2 * ncand && rc == MPDATA_OK; kk++) {
-        int k = kk % ncand;
-        int th = cand[k];
-        if (th > plan->g.n[0] && k > 0) continue;
+    for (int kk = 0; kk < 2 * (ncand + 1) && rc == MPDATA_OK; kk++) {
+        const int k = kk % (ncand + 1);
+        const int th = k == 0 ? own : cand[k - 1];
+        if (th == 0 || (k > 0 && th == own)) continue;
+        if (th > plan->g.n[0] && (own != 0 || k > 1)) continue;
         plan->tile_rows = th;
         const int reps = 5;
         for (int r = 0; r <= reps && rc == MPDATA_OK; r++) {
             if (r == 1) (void)hipEventRecord(e0, plan->stream);
-            if (plan->desc.dtype == MPDATA_F64)
-                rc = one_step<double>(plan, (const double *)psi, (double *)plan->L.psi_alt,
-                                      (const double *)g, (const double *)c0, (const double *)c1,
-                                      (const double *)c2, PATH_FUSED);
-            else
-                rc = one_step<float>(plan, (const float *)psi, (float *)plan->L.psi_alt,
-                                     (const float *)g, (const float *)c0, (const float *)c1,
-                                     (const float *)c2, PATH_FUSED);
+            rc = step();
         }
         if (rc) break;
         (void)hipEventRecord(e1, plan->stream);

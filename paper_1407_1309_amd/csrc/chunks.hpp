@@ -88,14 +88,17 @@ inline int64_t usual_rows(int64_t n0, int64_t strips, int64_t waves, int64_t lea
     return th < least ? least : th;
 }
 
+// shortest chunk of a fused step that also forms the step's diagnostics: their
+// partials' buffer is sized by it
+constexpr int FUSED2D_DIAG_ROWS = 16;
+
 // The fused step of n_iters passes: a chunk runs th + 2 LAG + 1 iterations,
-// of which the warm-up ones (W) do part of the work.  With diagnostics a
-// chunk is at least as long as the partials' buffer allows for.
+// of which the warm-up ones (W) do part of the work.
 inline int64_t fused2d_rows(int64_t n0, int64_t strips, const Slots &sl, int n_iters, bool f64,
                             bool diag)
 {
     const int np = n_iters - 1, lag = 1 + 2 * np, w = np == 0 ? 0 : 4 * np - 1;
-    const March2D m{2 * lag + 1 - w, n_iters <= 3 ? 4 : 8, diag ? 16 : 4, 0.75 * w,
+    const March2D m{2 * lag + 1 - w, n_iters <= 3 ? 4 : 8, diag ? FUSED2D_DIAG_ROWS : 4, 0.75 * w,
                     np == 0 ? 0.0 : f64 ? 0.375 : 0.75};
     return march_rows(n0, strips, sl, m, usual_rows(n0, strips, 2048, 16));
 }

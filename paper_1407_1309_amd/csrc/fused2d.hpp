@@ -628,7 +628,9 @@ hipError_t launch(const Fused2DShape &sh, const T *psi_n, T *psi_out, const T *c
                                     decltype(DG)::value);
             });
         }
+        if (decltype(DG)::value && th < FUSED2D_DIAG_ROWS) th = FUSED2D_DIAG_ROWS;
         if (th > sh.n0) th = sh.n0;
+        if (sh.rows_used) *sh.rows_used = (int)th;
         const int64_t blocks = strips * cdiv(sh.n0, th);
         if (dparts) *dparts = (int)blocks;
         kern<<<(unsigned)blocks, WAVE, 0, s>>>((int)sh.n0, (int)sh.n1, (int)th, (int)strips, psi_n,

@@ -126,13 +126,14 @@ bool fused3d_supported(int nd, int n_iters, unsigned opts, const int64_t n[3], c
 template <typename T>
 hipError_t fused3d_step(const Geom &geom, int n_iters, unsigned opts, const T *psi_n, T *psi_out,
                         const T *c0, const T *c1, const T *c2, const T *G, int tile_planes,
-                        hipStream_t s, const Fused3DWork<T> &w)
+                        hipStream_t s, const Fused3DWork<T> &w, int *planes_used)
 {
     if (n_iters >= 2) {
         if (!step3d_supported(geom.nd, n_iters, opts, geom.n)) return hipErrorNotSupported;
         const bool fct = opts & OPT_FCT;
         if (n_iters == 2 && !fct)
-            return step3d_launch<T>(geom, opts, psi_n, psi_out, c0, c1, c2, G, tile_planes, s);
+            return step3d_launch<T>(geom, opts, psi_n, psi_out, c0, c1, c2, G, tile_planes, s,
+                                    Step3dOut<T>(), planes_used);
         // pass by pass: the 3-D kernel forms the pass's raw
         // pseudo-velocities (pass 2 from the donor pass it forms itself,
         // which it also writes; later passes from the previous result) and
@@ -161,7 +162,8 @@ hipError_t fused3d_step(const Geom &geom, int n_iters, unsigned opts, const T *p
                 vo.bdn = w.bdn;
             }
             hipError_t e = step3d_launch<T>(geom, opts & ~OPT_FCT, psi_n, nullptr, adv[0], adv[1],
-                                            adv[2], G, tile_planes, s, vo);
+                                            adv[2], G, tile_planes, s, vo,
+                                            it == 2 ? planes_used : nullptr);
             if (e != hipSuccess) return e;
             const T *xp = x ? x : w.cell[0];
             T *y = last ? psi_out : w.cell[1 - xs];
@@ -203,10 +205,10 @@ hipError_t fused3d_step(const Geom &geom, int n_iters, unsigned opts, const T *p
 template hipError_t fused3d_step<float>(const Geom &, int, unsigned, const float *, float *,
                                         const float *, const float *, const float *,
                                         const float *, int, hipStream_t,
-                                        const Fused3DWork<float> &);
+                                        const Fused3DWork<float> &, int *);
 template hipError_t fused3d_step<double>(const Geom &, int, unsigned, const double *, double *,
                                          const double *, const double *, const double *,
                                          const double *, int, hipStream_t,
-                                         const Fused3DWork<double> &);
+                                         const Fused3DWork<double> &, int *);
 
 }  // namespace mp

@@ -79,6 +79,7 @@ struct Fused2DShape {
     int64_t n0, n1;      // rows (slow), columns (fast)
     int bc0, bc1;
     int tile_rows;       // rows per wavefront chunk; 0 = built-in default
+    int *rows_used = nullptr;   // receives the rows the launch took
 };
 
 // true if a fused kernel exists for this configuration
@@ -118,7 +119,7 @@ bool step3d_supported(int nd, int n_iters, unsigned opts, const int64_t n[3]);
 template <typename T>
 hipError_t step3d_launch(const Geom &g, unsigned opts, const T *psi_n, T *psi_out, const T *c0,
                          const T *c1, const T *c2, const T *G, int tile_planes, hipStream_t s,
-                         const Step3dOut<T> &vo = Step3dOut<T>());
+                         const Step3dOut<T> &vo = Step3dOut<T>(), int *planes_used = nullptr);
 // workspace of the 3-D step by passes: two cell fields, two sets of wall
 // fields, the limiter coefficients
 template <typename T> struct Fused3DWork {
@@ -128,7 +129,7 @@ bool fused3d_supported(int nd, int n_iters, unsigned opts, const int64_t n[3], c
 template <typename T>
 hipError_t fused3d_step(const Geom &g, int n_iters, unsigned opts, const T *psi_n, T *psi_out,
                         const T *c0, const T *c1, const T *c2, const T *G, int tile_planes,
-                        hipStream_t s, const Fused3DWork<T> &w);
+                        hipStream_t s, const Fused3DWork<T> &w, int *planes_used = nullptr);
 // the limited corrective donor-cell pass of a pass from its input x, raw
 // pseudo-velocities V and limiter coefficients: x -> y; W (entries NULL: not
 // wanted) receives the limited velocities, the next pass's advector

@@ -784,7 +784,7 @@ bool step3d_supported(int nd, int n_iters, unsigned opts, const int64_t n[3])
 template <typename T>
 hipError_t step3d_launch(const Geom &geom, unsigned opts, const T *psi_n, T *psi_out, const T *c0,
                          const T *c1, const T *c2, const T *G, int tile_planes, hipStream_t s,
-                         const Step3dOut<T> &vo)
+                         const Step3dOut<T> &vo, int *planes_used)
 {
     // the coefficients are formed only in output mode
     if (vo.bup && (!vo.bdn || !vo.v0)) return hipErrorInvalidValue;
@@ -808,6 +808,7 @@ hipError_t step3d_launch(const Geom &geom, unsigned opts, const T *psi_n, T *psi
             });
         }
         if (th > g.n0) th = g.n0;
+        if (planes_used) *planes_used = th;
         const int64_t blocks = tiles * cdiv(g.n0, th);
         if (blocks > INT32_MAX) {
             err = hipErrorInvalidValue;
@@ -849,10 +850,10 @@ hipError_t step3d_launch(const Geom &geom, unsigned opts, const T *psi_n, T *psi
 template hipError_t step3d_launch<float>(const Geom &, unsigned, const float *, float *,
                                          const float *, const float *, const float *,
                                          const float *, int, hipStream_t,
-                                         const Step3dOut<float> &);
+                                         const Step3dOut<float> &, int *);
 template hipError_t step3d_launch<double>(const Geom &, unsigned, const double *, double *,
                                           const double *, const double *, const double *,
                                           const double *, int, hipStream_t,
-                                          const Step3dOut<double> &);
+                                          const Step3dOut<double> &, int *);
 
 }  // namespace mp
