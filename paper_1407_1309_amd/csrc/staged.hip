@@ -389,12 +389,17 @@ __global__ void __launch_bounds__(256) k_fct_limit(Geom g, const T *__restrict__
 // then W0..W2 (non-NULL) receive each cell's low walls and, along an open
 // dimension, the far edge wall.  mode bit 0: the flux is the limited
 // velocity itself (infinite gauge); bit 1: Kahan-compensated update.
+// Contraction is off here and in k_limcorr3d, so that the two, and any other
+// writing of the same terms, give the same bits: left to the compiler, a flux
+// is fused with the difference it goes into where the code is straight and not
+// where a branch lies between them.
 template <typename T, int ND>
 __global__ void __launch_bounds__(256)
 k_limcorr(Geom g, const T *__restrict__ x, const T *V0, const T *V1, const T *V2,
           const T *__restrict__ bup, const T *__restrict__ bdn, const T *G, int mode,
           T *__restrict__ out, T *W0, T *W1, T *W2)
 {
+#pragma clang fp contract(off)
     const int64_t N = g.n[0] * g.n[1] * g.n[2];
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= N) return;
@@ -453,6 +458,7 @@ k_limcorr3d(int n0, int n1, int n2, int bc0, int bc1, int bc2, const T *__restri
             const T *__restrict__ bup, const T *__restrict__ bdn, const T *__restrict__ G,
             int mode, T *__restrict__ out, T *W0, T *W1, T *W2)
 {
+#pragma clang fp contract(off)
     const int q = blockIdx.x * 256 + threadIdx.x;
     if (q >= n1 * n2) return;
     const bool kahan = mode & 2;
