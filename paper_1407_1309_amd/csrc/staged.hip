@@ -535,14 +535,17 @@ Slots slots_of(const void *kernel, int threads, size_t lds)
 {
     Slots v{256, 1};
     int dev = 0, cus = 0, per = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        cus > 0)
-        v.cus = cus;
-    if (kernel && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds) ==
-                      hipSuccess && per > 0)
-        v.per_cu = per;
-    (void)hipGetLastError();
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess && cus > 0) v.cus = cus;
+    hipError_t k = hipSuccess;
+    if (kernel) {
+        k = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds);
+        if (k == hipSuccess && per > 0) v.per_cu = per;
+    }
+    // only what these queries raised is cleared: an error that the caller has
+    // pending stays for the launch's own check
+    if (e != hipSuccess || k != hipSuccess) (void)hipGetLastError();
     return v;
 }
 
