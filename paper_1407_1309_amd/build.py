@@ -38,30 +38,31 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
-KERNEL_SOURCE = {"k_fused2d": "fused2d.hpp", "k_fused2d_batched": "fused2d.hpp",
-                 "k_step3d": "step3d.hip", "k_donor3d": "fused3d.hip",
-                 "k_resident1d": "line1d.hpp",
-                 "k_pass2d": "pass2d.hpp", "k_donor2d": "pass2d.hip"}
+# what a kernel is made of: the files that define it, instantiate it and choose
+# its launch shape (common.hpp besides)
+_FUSED2D_FILES = ["fused2d.hpp", "fused2d_f32.hip", "fused2d_f64.hip", "chunks.hpp"]
+KERNEL_SOURCES = {
+    "k_fused2d": _FUSED2D_FILES, "k_fused2d_batched": _FUSED2D_FILES,
+    "k_step3d": ["step3d.hip"], "k_donor3d": ["fused3d.hip"],
+    "k_resident1d": ["line1d.hpp", "resident1d.hip", "resident1d_f32.hip"],
+    "k_pass2d": ["pass2d.hpp", "pass2d.hip", "chunks.hpp",
+                 *(f"pass2d_{t}_{d}.hip" for t in ("f64", "f32") for d in ("donor", "pass"))],
+    "k_donor2d": ["pass2d.hip"]}
 
 
 def source_hash(kernel=None):
-    """SHA-256 over the kernel sources (used to tie stored counter readings to
-    the code they were taken from): the file that defines `kernel` plus the
-    shared header, or every source when kernel is None or unknown."""
+    """SHA-256 over the kernel sources and device flags (used to tie stored
+    counter readings to the code they were taken from): the files of `kernel`
+    and the shared header, or every source when kernel is None or unknown."""
     import hashlib
     h = hashlib.sha256()
-    own = KERNEL_SOURCE.get(kernel)
+    own = KERNEL_SOURCES.get(kernel)
     for f in sorted(os.listdir(CSRC)):
-        if own is not None and f not in (own, "common.hpp"):
+        if not f.endswith((".hip", ".hpp")) or (own and f not in own and f != "common.hpp"):
             continue
-        if f.endswith((".hip", ".hpp")):
-            h.update(f.encode())
-            h.update(open(os.path.join(CSRC, f), "rb").read())
-    # the device flags of the files that instantiate the kernel
-    stem = own.rsplit(".", 1)[0] if own else ""
-    for f in sorted(FILE_FLAGS):
-        if own is None or f.startswith(stem):
-            h.update(" ".join(FILE_FLAGS[f]).encode())
+        h.update(f.encode())
+        h.update(open(os.path.join(CSRC, f), "rb").read())
+        h.update(" ".join(FILE_FLAGS.get(f, [])).encode())
     return h.hexdigest()[:16]
 
 
