@@ -73,6 +73,9 @@ hipError_t pass2d_launch(const Geom &g, unsigned opts, const T *x, const T *c0, 
     return psi_n ? pass2d_go<T, false>(p) : pass2d_go<T, true>(p);
 }
 
+// the option sets of the shallow-water examples (Sect. 5.4), whose variants
+// of the pass carry the saving store; another set's fields are advected by a
+// launch each
 bool pass2d_saves(unsigned opts)
 {
     return opts == (OPT_FCT | OPT_IGA | OPT_DFL) || opts == (OPT_FCT | OPT_ABS);

@@ -867,7 +867,13 @@ template <typename T, bool DONOR> hipError_t pass2d_go(const PassArgs<T> &p)
         return p.G ? by_t(F, I, A, TT{}) : by_t(F, I, A, FF{});
     };
     auto by_f = [&](auto I, auto A) { return fct ? by_g(TT{}, I, A) : by_g(FF{}, I, A); };
-    if (iga) return by_f(TT{}, FF{});
+    // (the infinite gauge has two passes at most, and the second one always
+    // comes with the donor pass)
+    if constexpr (DONOR) {
+        if (iga) return by_f(TT{}, FF{});
+    } else if (iga) {
+        return hipErrorInvalidValue;
+    }
     if (absf) return by_f(FF{}, TT{});
     return by_f(FF{}, FF{});
 }

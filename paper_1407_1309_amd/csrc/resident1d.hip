@@ -14,10 +14,18 @@ int line_own(int radius, int K) { return (WAVE - 2 * line_halo_lanes(radius, K))
 
 bool resident1d_supported(int nd, int64_t n, int dtype_is_f64, int has_g, int two_fields)
 {
-    // The grids that run every step of a call in one launch: one workgroup's
-    // waves hold 3328 FP64 or 7424 FP32 cells at the largest radius, more
-    // than this bound admits; beyond about the bound the tiled launches are
-    // the faster ones, whatever the number of steps.
+    // The grids that run every step of a call in one launch, in place (what
+    // KERNEL_FUSED admits, and where the cancel flag is read once a call).
+    // One workgroup's waves hold 3328 FP64 or 7424 FP32 cells at the largest
+    // radius; the bound is lower, that of a kernel that kept nine fields in
+    // LDS, so that the same grids run this way as did with it.  It is not
+    // where the two ways cross: one workgroup is the faster one for a few
+    // steps, on either side of it, and tiles are for many.  us per call,
+    // limiter, two passes, one workgroup / tiles: 2275 cells FP64 1 step 9.3 /
+    // 11.7, 5 steps 15 / 12, 20 steps 50 / 13, 100 steps 237 / 51; 1000 cells
+    // 1 step 9.0 / 11.6, 20 steps 28 / 13, 100 steps 131 / 50; 4550 cells
+    // FP32 1 step 10.2 / 11.7, 100 steps 352 / 45; 6000 cells FP32 1 step
+    // 12.6 / 11.4.
     if (nd != 1 || n < 1 || n > (1 << 20)) return false;
     const size_t fields = 9 + (has_g ? 1 : 0) + (two_fields ? 1 : 0);
     return (dtype_is_f64 ? 8 : 4) * (fields * (size_t)n + 4) <= 160 * 1024;
