@@ -15,7 +15,7 @@ FCT, IGA, TOT = mpdata.OPT_FCT, mpdata.OPT_IGA, mpdata.OPT_TOT
 
 def _us_per_step(plan, start, c, g, n=20):
     best = 1e30
-    for _ in range(7):
+    for _ in range(20):
         p = start.clone()
         a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
         a.record()
